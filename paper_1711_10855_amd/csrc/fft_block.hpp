@@ -140,6 +140,26 @@ __device__ __forceinline__ void exchange(c32 (&d)[Gm::E], c32 *buf0, c32 *buf1, 
   }
 }
 
+// The two halves of an exchange, for callers that place the ordering
+// between them themselves: registers in the layout of stage A to a buffer,
+// and a buffer to registers in the layout of stage B.
+template <class Gm, int A>
+__device__ __forceinline__ void exchange_put(const c32 (&d)[Gm::E], c32 *buf, int t) {
+  constexpr int R = Gm::R[A];
+#pragma unroll
+  for (int j = 0; j < Gm::B(A); ++j)
+#pragma unroll
+    for (int n = 0; n < R; ++n) buf[pad<Gm>(stage_addr<Gm, A>(t, j, n))] = d[j * R + n];
+}
+template <class Gm, int B>
+__device__ __forceinline__ void exchange_get(c32 (&d)[Gm::E], const c32 *buf, int t) {
+  constexpr int R = Gm::R[B];
+#pragma unroll
+  for (int j = 0; j < Gm::B(B); ++j)
+#pragma unroll
+    for (int n = 0; n < R; ++n) d[j * R + n] = buf[pad<Gm>(stage_addr<Gm, B>(t, j, n))];
+}
+
 // Buffer parity bookkeeping: the number of block-wide exchanges among the
 // exchanges with lower stage index in [a, b) (each flips the buffer when
 // there are two).

@@ -16,6 +16,18 @@
 // elements in VGPRs, the first inverse stage consumes the forward result
 // without touching LDS, and only the remaining P - 1 stages exchange
 // through a padded LDS buffer.
+//
+// Templates z and -z are complex conjugates at integer offsets and even in
+// the offset, so their bank rows are conjugates too. A unit of the pair form
+// takes them two at a time: one bank row serves both, and the two inverse
+// transforms are independent, so one's butterflies run while the other's
+// LDS exchange is in flight, on half as many bank loads and barriers. The
+// kernel is bound by FP32 vector issue (88% busy at 2048 points); the pair
+// form takes part of the rest. Measured at 2^20 bins (2^21 at 2048), single
+// form -> pair form: 256 points 30.2 -> 27.9 us (17 rows), 512 points 143 ->
+// 131 us, 1024 points 153 -> 141 us, 2048 points 306 -> 291 us (101 rows).
+// At 4096 points its registers spill (316 -> 334 us), so that length keeps
+// the single form, as do half-bin plans, whose odd rows are no conjugates.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -42,12 +54,14 @@ __device__ __forceinline__ T *uniform_ptr(T *p) {
 // One work unit: segment s of a spectrum, bank rows [z0, z1), plane rows
 // (iz - row_base). The unit starts on LDS buffer 0: its caller guarantees a
 // block barrier since any earlier unit's last LDS read.
-template <class Gm, bool TWREG, bool PF, bool CAND>
+// PAIR: [z0, z1) lies in the first half (rounded up) of the series' `rows`
+// bank rows from row_base on, and each row comes with its mirror row.
+template <class Gm, bool TWREG, bool PF, bool CAND, bool PAIR>
 __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t nbins,
                                          const c32 *__restrict__ bank_, const c32 *__restrict__ tw_,
                                          float *__restrict__ power_, int64_t ld, int s, bool active,
-                                         int U, int half, int z0, int z1, int row_base, c32 *buf0,
-                                         c32 *buf1, int t, const CandOut &cd) {
+                                         int U, int half, int z0, int z1, int row_base, int rows,
+                                         c32 *buf0, c32 *buf1, int t, const CandOut &cd) {
   const auto spec = to_global(spec_);
   const auto bank = to_global(bank_);
   const auto tw = to_global(tw_);
@@ -84,8 +98,8 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
     return c32{v.x, v.y};
   };
 
-  c32 bnext[PF ? E : 1];
-  if constexpr (PF) {
+  c32 bnext[PF && !PAIR ? E : 1];
+  if constexpr (PF && !PAIR) {
     const auto rs = bank_row(z0);
 #pragma unroll
     for (int e = 0; e < E; ++e) bnext[e] = bank_elem(rs, e);
@@ -143,6 +157,69 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
       }
   }
 
+  // Powers of one template from its outputs: slot j*R0 + n holds index
+  // n * S0 + t + j T of the segment.
+  auto emit = [&](int iz, const c32 (&y)[E]) {
+    if constexpr (CAND) {
+      // detection epilogue: one ballot on the lane's largest power skips a
+      // wave with no hit at all (the common case), else every lane takes part
+      // in each offer (one atomic per wave that has a hit)
+      constexpr int S0 = Gm::S(0), R0 = Gm::R[0];
+      float pw[E], most = 0.f;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        pw[e] = __builtin_fmaf(y[e].x, y[e].x, y[e].y * y[e].y);
+        most = e ? fmaxf(most, pw[e]) : pw[e];
+      }
+      if (__builtin_amdgcn_ballot_w64(active && most >= cd.thr) != 0ull) {
+#pragma nounroll
+        for (int e = 0; e < E; ++e) {
+          const int o = (e % R0) * S0 + t + (e / R0) * T;
+          const int64_t r = (int64_t)s * U + o - half;
+          const bool hit = active && o >= half && o < half + U && r < nbins && pw[e] >= cd.thr;
+          cand_offer(cd, hit, iz - row_base, r, pw[e]);
+        }
+      }
+    } else if (kBufStore && active) {
+      // Stores through a buffer resource that starts at plane column s U
+      // (segment output `half`) and spans the segment's kept outputs: output
+      // o goes to byte offset (o - half) * 4, which is negative (so, taken as
+      // unsigned, past the end) for o < half and at or past the end for
+      // o >= half + U or beyond nbins, and the hardware drops those lanes.
+      // (With T >= 64 a wave holds one segment, so s is the same in every
+      // lane and the resource is wave-uniform.)
+      constexpr int S0 = Gm::S(0), R0 = Gm::R[0];
+      const int su = __builtin_amdgcn_readfirstlane(s);
+      const int64_t left = nbins - (int64_t)su * U;
+      const int nkeep = (int)(left < U ? left : U);
+      const auto rs = __builtin_amdgcn_make_buffer_rsrc(
+          uniform_ptr(power_ + (int64_t)(iz - row_base) * ld + (int64_t)su * U), (short)0, nkeep * 4,
+          0x00020000);
+#pragma unroll
+      for (int j = 0; j < Gm::B(0); ++j)
+#pragma unroll
+        for (int n = 0; n < R0; ++n) {
+          const c32 v = y[j * R0 + n];
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(__builtin_fmaf(v.x, v.x, v.y * v.y)),
+                                                rs, soff[j * R0 + n], 0, 2 /* nontemporal */);
+        }
+    } else if (active) {  // segments narrower than a wave: per-lane addresses
+      constexpr int S0 = Gm::S(0), R0 = Gm::R[0];
+      const auto prow = power + (int64_t)(iz - row_base) * ld;
+#pragma unroll
+      for (int j = 0; j < Gm::B(0); ++j)
+#pragma unroll
+        for (int n = 0; n < R0; ++n) {
+          const int o = n * S0 + t + j * T;
+          const int64_t r = (int64_t)s * U + o - half;
+          if (o >= half && o < half + U && r < nbins) {
+            const c32 v = y[j * R0 + n];
+            __builtin_nontemporal_store(__builtin_fmaf(v.x, v.x, v.y * v.y), prow + r);
+          }
+        }
+    }
+  };
+
   // one template; P0 is the buffer parity at its start
   auto one = [&](int iz, auto p0c) {
     constexpr int P0 = decltype(p0c)::value;
@@ -191,73 +268,90 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
       }
     });
 
-    // outputs: slot j*R0 + n holds index n * S0 + t + j T of the segment
-    if constexpr (CAND) {
-      // detection epilogue: the powers first (the transform's registers are
-      // then free), one ballot to skip a wave with no hit at all (the common
-      // case), else every lane takes part in each offer (one atomic per wave
-      // that has a hit)
-      constexpr int S0 = Gm::S(0), R0 = Gm::R[0];
-      float pw[E];
-      bool any = false;
+    emit(iz, y);
+  };
+  // Pair form: template iz through buf0 and its mirror (the conjugate bank
+  // row) through buf1. A wave-local exchange reads back at once, so that its
+  // latency passes under the other transform's butterflies; a block-wide one
+  // takes one barrier for both, and another before the buffers are written
+  // again (two barriers per pair). The bank row is loaded into the registers
+  // it was used from, as soon as both products have read it.
+  auto pair_loop = [&]() {
+    c32 bt[E];
+    auto load_row = [&](int iz) {
+      const auto rs = bank_row(iz);
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        pw[e] = __builtin_fmaf(y[e].x, y[e].x, y[e].y * y[e].y);
-        any |= pw[e] >= cd.thr;
-      }
-      if (__builtin_amdgcn_ballot_w64(active && any) != 0ull) {
+      for (int e = 0; e < E; ++e) bt[e] = bank_elem(rs, e);
+    };
+    auto stage = [&](c32 (&y)[E], auto ic, auto conj) {
+      constexpr int I = decltype(ic)::value;
+      constexpr int R = Gm::R[I];
+      if constexpr (I == P - 1) {
+        // (the sign goes into the multiply-adds: the same operations, so the
+        // same bits, as with the mirror's own row)
+        c32 b[E];
 #pragma unroll
-        for (int j = 0; j < Gm::B(0); ++j)
-#pragma unroll
-          for (int n = 0; n < R0; ++n) {
-            const int o = n * S0 + t + j * T;
-            const int64_t r = (int64_t)s * U + o - half;
-            const float p = pw[j * R0 + n];
-            const bool hit = active && o >= half && o < half + U && r < nbins && p >= cd.thr;
-            cand_offer(cd, hit, iz - row_base, r, p);
-          }
-      }
-    } else if (kBufStore && active) {
-      // Stores through a buffer resource that starts at plane column s U
-      // (segment output `half`) and spans the segment's kept outputs: output
-      // o goes to byte offset (o - half) * 4, which is negative (so, taken as
-      // unsigned, past the end) for o < half and at or past the end for
-      // o >= half + U or beyond nbins, and the hardware drops those lanes.
-      // (With T >= 64 a wave holds one segment, so s is the same in every
-      // lane and the resource is wave-uniform.)
-      constexpr int S0 = Gm::S(0), R0 = Gm::R[0];
-      const int su = __builtin_amdgcn_readfirstlane(s);
-      const int64_t left = nbins - (int64_t)su * U;
-      const int nkeep = (int)(left < U ? left : U);
-      const auto rs = __builtin_amdgcn_make_buffer_rsrc(
-          uniform_ptr(power_ + (int64_t)(iz - row_base) * ld + (int64_t)su * U), (short)0, nkeep * 4,
-          0x00020000);
-#pragma unroll
-      for (int j = 0; j < Gm::B(0); ++j)
-#pragma unroll
-        for (int n = 0; n < R0; ++n) {
-          const c32 v = y[j * R0 + n];
-          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(__builtin_fmaf(v.x, v.x, v.y * v.y)),
-                                                rs, soff[j * R0 + n], 0, 2 /* nontemporal */);
+        for (int e = 0; e < E; ++e) {
+          y[e] = x[e];
+          b[e] = {bt[e].x, decltype(conj)::value ? -bt[e].y : bt[e].y};
         }
-    } else if (active) {  // segments narrower than a wave: per-lane addresses
-      constexpr int S0 = Gm::S(0), R0 = Gm::R[0];
-      const auto prow = power + (int64_t)(iz - row_base) * ld;
 #pragma unroll
-      for (int j = 0; j < Gm::B(0); ++j)
+        for (int j = 0; j < Gm::B(I); ++j) dft_tw<+1, false, R, true>(&y[j * R], &b[j * R]);
+      } else {
+        constexpr int N = R * Gm::S(I);
 #pragma unroll
-        for (int n = 0; n < R0; ++n) {
-          const int o = n * S0 + t + j * T;
-          const int64_t r = (int64_t)s * U + o - half;
-          if (o >= half && o < half + U && r < nbins) {
-            const c32 v = y[j * R0 + n];
-            __builtin_nontemporal_store(__builtin_fmaf(v.x, v.x, v.y * v.y), prow + r);
+        for (int j = 0; j < Gm::B(I); ++j) {
+          const int mi = stage_suffix<Gm, I>(t, j);
+          c32 w[R];
+#pragma unroll
+          for (int k = 1; k < R; ++k)
+            w[k] = TWREG ? itw[Gm::TWOFF(I) + j * (R - 1) + k - 1] : ldg(tw + (k * mi) * (L / N));
+          dft_tw<+1, true, R>(&y[j * R], w);
+        }
+      }
+    };
+    if (z0 < z1) load_row(z0);
+    const int mirror = 2 * row_base + rows - 1;
+    for (int iz = z0; iz < z1; ++iz) {
+      c32 ya[E], yb[E];
+      static_for_down<P - 1, 0>([&](auto ic) {
+        constexpr int I = decltype(ic)::value;
+        stage(ya, ic, std::false_type{});
+        if constexpr (I > 0) {
+          // the first write after a block-wide read: every wave must have read
+          constexpr bool free_first = I == P - 1 ? Gm::any_block() : !Gm::local(I);
+          if constexpr (free_first) __syncthreads();
+          exchange_put<Gm, I>(ya, buf0, t);
+          if constexpr (Gm::local(I - 1)) {
+            wave_sync();
+            exchange_get<Gm, I - 1>(ya, buf0, t);
           }
         }
+        stage(yb, ic, std::true_type{});
+        // (the last pair reloads its own row: an unconditional load)
+        if constexpr (I == P - 1) load_row(iz + 1 < z1 ? iz + 1 : iz);
+        if constexpr (I > 0) {
+          exchange_put<Gm, I>(yb, buf1, t);
+          if constexpr (Gm::local(I - 1)) {
+            wave_sync();
+            exchange_get<Gm, I - 1>(yb, buf1, t);
+          } else {
+            __syncthreads();
+            exchange_get<Gm, I - 1>(ya, buf0, t);
+            exchange_get<Gm, I - 1>(yb, buf1, t);
+          }
+        }
+      });
+      emit(iz, ya);
+      if (mirror - iz != iz) emit(mirror - iz, yb);  // (z = 0 is its own mirror)
+      // wave-local exchanges only: this wave's next writes after its reads
+      if constexpr (!Gm::any_block()) wave_sync();
     }
   };
   constexpr int PF0 = flips<Gm>(0, P - 1) & 1;  // after the forward transform
-  if constexpr ((flips<Gm>(0, P - 1) & 1) == 0) {
+  if constexpr (PAIR) {
+    pair_loop();
+  } else if constexpr ((flips<Gm>(0, P - 1) & 1) == 0) {
     for (int iz = z0; iz < z1; ++iz) one(iz, std::integral_constant<int, PF0>{});
   } else {
     // an odd number of flips per template: alternate the two parities
@@ -272,12 +366,12 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
 
 // Single spectrum: block -> (segment group, template group), template-group
 // major so concurrently running blocks share bank rows in L2.
-template <class Gm, int G, bool TWREG, bool PF, int WPE, bool CAND>
+template <class Gm, int G, bool TWREG, bool PF, int WPE, bool CAND, bool PAIR>
 __global__ void __launch_bounds__(Gm::T *G) __attribute__((amdgpu_waves_per_eu(WPE)))
     ols_fp32_kernel(const c32 *__restrict__ spec, int64_t nbins, const c32 *__restrict__ bank,
                     const c32 *__restrict__ tw, float *__restrict__ power, int64_t ld, int nseg,
                     int U, int half, int nz, int zpb, int nsb, CandOut cand) {
-  constexpr int T = Gm::T, NB = Gm::NBUF;
+  constexpr int T = Gm::T, NB = PAIR ? 2 : Gm::NBUF;
   __shared__ c32 lds[NB][G][Gm::LP];
   const int tid = threadIdx.x;
   const int sg = tid / T;
@@ -286,21 +380,21 @@ __global__ void __launch_bounds__(Gm::T *G) __attribute__((amdgpu_waves_per_eu(W
   const int zg = blockIdx.x / nsb;
   const int s = sb * G + sg;
   const int z0 = zg * zpb;
-  const int z1 = min(nz, z0 + zpb);
-  ols_unit<Gm, TWREG, PF, CAND>(spec, nbins, bank, tw, power, ld, s, s < nseg, U, half, z0, z1, 0,
-                          lds[0][sg], lds[NB - 1][sg], t, cand);
+  const int z1 = min(unit_rows(nz, PAIR), z0 + zpb);
+  ols_unit<Gm, TWREG, PF, CAND, PAIR>(spec, nbins, bank, tw, power, ld, s, s < nseg, U, half, z0,
+                                      z1, 0, nz, lds[0][sg], lds[NB - 1][sg], t, cand);
 }
 
 // Batch: persistent blocks take work items (series, template group, segment
 // group) from a device counter until the list is exhausted. Items are
 // numbered series by series (largest first on the host), template-group major
 // inside a series.
-template <class Gm, int G, bool TWREG, bool PF, int WPE>
+template <class Gm, int G, bool TWREG, bool PF, int WPE, bool PAIR>
 __global__ void __launch_bounds__(Gm::T *G) __attribute__((amdgpu_waves_per_eu(WPE)))
     ols_fp32_batch_kernel(const SeriesDesc *__restrict__ desc, int nseries, int64_t total,
                           unsigned long long *__restrict__ counter, const c32 *__restrict__ bank,
                           const c32 *__restrict__ tw, int U, int half, int zpb) {
-  constexpr int T = Gm::T, NB = Gm::NBUF;
+  constexpr int T = Gm::T, NB = PAIR ? 2 : Gm::NBUF;
   __shared__ c32 lds[NB][G][Gm::LP];
   __shared__ long long s_item[2];
   const int tid = threadIdx.x;
@@ -331,12 +425,14 @@ __global__ void __launch_bounds__(Gm::T *G) __attribute__((amdgpu_waves_per_eu(W
     const int sg = tid_i / T;
     const int t = tid_i % T;
     const int s = sb * G + sg;
-    const int z0 = d.row_off + zg * d.zpb;
-    const int z1 = min(d.row_off + d.nz, z0 + d.zpb);
+    const int per = unit_rows(d.zpb, PAIR);
+    const int z0 = d.row_off + zg * per;
+    const int z1 = min(d.row_off + unit_rows(d.nz, PAIR), z0 + per);
     const CandOut none{};
-    ols_unit<Gm, TWREG, PF, false>(static_cast<const c32 *>(d.spec), d.nbins, opaque_ptr(bank),
-                            opaque_ptr(tw), d.power, d.ld, s, s < d.nseg, U, half, z0, z1,
-                            d.row_off, lds[0][sg], lds[NB - 1][sg], t, none);
+    ols_unit<Gm, TWREG, PF, false, PAIR>(static_cast<const c32 *>(d.spec), d.nbins,
+                                         opaque_ptr(bank), opaque_ptr(tw), d.power, d.ld, s,
+                                         s < d.nseg, U, half, z0, z1, d.row_off, d.nz, lds[0][sg],
+                                         lds[NB - 1][sg], t, none);
   }
 }
 
@@ -344,12 +440,12 @@ __global__ void __launch_bounds__(Gm::T *G) __attribute__((amdgpu_waves_per_eu(W
 // the hardware dispatcher hands out items in order as blocks retire
 // (FDAS_BATCH_PERSISTENT=0; the persistent loop above is the default, 1%
 // faster on the batched workloads).
-template <class Gm, int G, bool TWREG, bool PF, int WPE>
+template <class Gm, int G, bool TWREG, bool PF, int WPE, bool PAIR>
 __global__ void __launch_bounds__(Gm::T *G) __attribute__((amdgpu_waves_per_eu(WPE)))
     ols_fp32_items_kernel(const SeriesDesc *__restrict__ desc, int nseries,
                           const c32 *__restrict__ bank, const c32 *__restrict__ tw, int U,
                           int half, int zpb) {
-  constexpr int T = Gm::T, NB = Gm::NBUF;
+  constexpr int T = Gm::T, NB = PAIR ? 2 : Gm::NBUF;
   __shared__ c32 lds[NB][G][Gm::LP];
   const int tid = threadIdx.x;
   const int sg = tid / T;
@@ -367,12 +463,13 @@ __global__ void __launch_bounds__(Gm::T *G) __attribute__((amdgpu_waves_per_eu(W
   const int zg = (int)(local / nsb);
   const int sb = (int)(local % nsb);
   const int s = sb * G + sg;
-  const int z0 = d.row_off + zg * d.zpb;
-  const int z1 = min(d.row_off + d.nz, z0 + d.zpb);
+  const int per = unit_rows(d.zpb, PAIR);
+  const int z0 = d.row_off + zg * per;
+  const int z1 = min(d.row_off + unit_rows(d.nz, PAIR), z0 + per);
   const CandOut none{};
-  ols_unit<Gm, TWREG, PF, false>(static_cast<const c32 *>(d.spec), d.nbins, bank, tw, d.power, d.ld, s,
-                          s < d.nseg, U, half, z0, z1, d.row_off, lds[0][sg], lds[NB - 1][sg],
-                          t, none);
+  ols_unit<Gm, TWREG, PF, false, PAIR>(static_cast<const c32 *>(d.spec), d.nbins, bank, tw, d.power,
+                                       d.ld, s, s < d.nseg, U, half, z0, z1, d.row_off, d.nz,
+                                       lds[0][sg], lds[NB - 1][sg], t, none);
 }
 
 __global__ void reset_counter_kernel(unsigned long long *counter) { *counter = 0ULL; }
@@ -388,64 +485,91 @@ static bool batch_persistent() {
 }
 
 // ---- variant registry ------------------------------------------------------
+// WPE: waves per SIMD the single form's registers are capped for (1: no cap);
+// PWPE: the same for the pair form, 0 where there is none.
 
-template <class Gm, int G, bool TWREG, bool PF, int WPE>
-static hipError_t launch_variant(const OlsArgs &a, hipStream_t st) {
+template <class Gm, int G, bool TWREG, bool PF, int WPE, bool CAND, bool PAIR>
+static hipError_t launch_form(const OlsArgs &a, hipStream_t st) {
   const int nsb = (a.nseg + G - 1) / G;
-  const int nzg = (a.nz + a.zpb - 1) / a.zpb;
+  const int per = unit_rows(a.zpb, PAIR);
+  const int nzg = (unit_rows(a.nz, PAIR) + per - 1) / per;
   const long blocks = (long)nsb * nzg;
-  if (a.cand.count)
-    hipLaunchKernelGGL((ols_fp32_kernel<Gm, G, TWREG, PF, WPE, true>), dim3((unsigned)blocks),
-                       dim3(Gm::T * G), 0, st, static_cast<const c32 *>(a.spec), a.nbins,
-                       static_cast<const c32 *>(a.bank), static_cast<const c32 *>(a.tw), a.power,
-                       a.ld, a.nseg, a.U, a.half, a.nz, a.zpb, nsb, a.cand);
-  else
-    hipLaunchKernelGGL((ols_fp32_kernel<Gm, G, TWREG, PF, WPE, false>), dim3((unsigned)blocks),
-                       dim3(Gm::T * G), 0, st, static_cast<const c32 *>(a.spec), a.nbins,
-                       static_cast<const c32 *>(a.bank), static_cast<const c32 *>(a.tw), a.power,
-                       a.ld, a.nseg, a.U, a.half, a.nz, a.zpb, nsb, a.cand);
+  hipLaunchKernelGGL((ols_fp32_kernel<Gm, G, TWREG, PF, WPE, CAND, PAIR>), dim3((unsigned)blocks),
+                     dim3(Gm::T * G), 0, st, static_cast<const c32 *>(a.spec), a.nbins,
+                     static_cast<const c32 *>(a.bank), static_cast<const c32 *>(a.tw), a.power,
+                     a.ld, a.nseg, a.U, a.half, a.nz, per, nsb, a.cand);
   return hipGetLastError();
 }
 
-template <class Gm, int G, bool TWREG, bool PF, int WPE>
-static hipError_t launch_batch_variant(const BatchArgs &a, hipStream_t st) {
+template <class Gm, int G, bool TWREG, bool PF, int WPE, int PWPE>
+static hipError_t launch_variant(const OlsArgs &a, hipStream_t st) {
+  if constexpr (PWPE > 0) {
+    if (a.pair)
+      return a.cand.count ? launch_form<Gm, G, TWREG, PF, PWPE, true, true>(a, st)
+                          : launch_form<Gm, G, TWREG, PF, PWPE, false, true>(a, st);
+  }
+  return a.cand.count ? launch_form<Gm, G, TWREG, PF, WPE, true, false>(a, st)
+                      : launch_form<Gm, G, TWREG, PF, WPE, false, false>(a, st);
+}
+
+template <class Gm, int G, bool TWREG, bool PF, int WPE, bool PAIR>
+static hipError_t launch_batch_form(const BatchArgs &a, hipStream_t st) {
   if (batch_persistent()) {
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, st, a.counter);
-    hipLaunchKernelGGL((ols_fp32_batch_kernel<Gm, G, TWREG, PF, WPE>), dim3((unsigned)a.grid),
+    hipLaunchKernelGGL((ols_fp32_batch_kernel<Gm, G, TWREG, PF, WPE, PAIR>), dim3((unsigned)a.grid),
                        dim3(Gm::T * G), 0, st, a.desc, a.nseries, a.total, a.counter,
                        static_cast<const c32 *>(a.bank), static_cast<const c32 *>(a.tw), a.U,
                        a.half, a.zpb);
   } else {
     if (a.total > (int64_t)0xffffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((ols_fp32_items_kernel<Gm, G, TWREG, PF, WPE>), dim3((unsigned)a.total),
-                       dim3(Gm::T * G), 0, st, a.desc, a.nseries,
+    hipLaunchKernelGGL((ols_fp32_items_kernel<Gm, G, TWREG, PF, WPE, PAIR>),
+                       dim3((unsigned)a.total), dim3(Gm::T * G), 0, st, a.desc, a.nseries,
                        static_cast<const c32 *>(a.bank), static_cast<const c32 *>(a.tw), a.U,
                        a.half, a.zpb);
   }
   return hipGetLastError();
 }
 
-template <class Gm, int G, bool TWREG, bool PF, int WPE>
-static int batch_blocks_per_cu() {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, reinterpret_cast<const void *>(&ols_fp32_batch_kernel<Gm, G, TWREG, PF, WPE>),
-          Gm::T * G, 0) != hipSuccess)
-    return 0;
-  return nb;
+template <class Gm, int G, bool TWREG, bool PF, int WPE, int PWPE>
+static hipError_t launch_batch_variant(const BatchArgs &a, hipStream_t st) {
+  if constexpr (PWPE > 0) {
+    if (a.pair) return launch_batch_form<Gm, G, TWREG, PF, PWPE, true>(a, st);
+  }
+  return launch_batch_form<Gm, G, TWREG, PF, WPE, false>(a, st);
 }
 
-template <class Gm, int G, bool TWREG, bool PF, int WPE>
-static int grid_blocks_per_cu() {
+static int blocks_per_cu(const void *kernel, int threads) {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, reinterpret_cast<const void *>(&ols_fp32_kernel<Gm, G, TWREG, PF, WPE, false>), Gm::T * G,
-          0) != hipSuccess)
-    return 0;
-  return nb;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, threads, 0) == hipSuccess ? nb : 0;
 }
 
-template <class Gm, int G, bool TWREG, bool PF, int WPE = 1>
+template <class Gm, int G, bool TWREG, bool PF, int WPE, int PWPE>
+static int batch_blocks_per_cu(int pair) {
+  if constexpr (PWPE > 0) {
+    if (pair)
+      return blocks_per_cu(
+          reinterpret_cast<const void *>(&ols_fp32_batch_kernel<Gm, G, TWREG, PF, PWPE, true>),
+          Gm::T * G);
+  }
+  return blocks_per_cu(
+      reinterpret_cast<const void *>(&ols_fp32_batch_kernel<Gm, G, TWREG, PF, WPE, false>),
+      Gm::T * G);
+}
+
+template <class Gm, int G, bool TWREG, bool PF, int WPE, int PWPE>
+static int grid_blocks_per_cu(int pair) {
+  if constexpr (PWPE > 0) {
+    if (pair)
+      return blocks_per_cu(
+          reinterpret_cast<const void *>(&ols_fp32_kernel<Gm, G, TWREG, PF, PWPE, false, true>),
+          Gm::T * G);
+  }
+  return blocks_per_cu(
+      reinterpret_cast<const void *>(&ols_fp32_kernel<Gm, G, TWREG, PF, WPE, false, false>),
+      Gm::T * G);
+}
+
+template <class Gm, int G, bool TWREG, bool PF, int WPE = 1, int PWPE = 0>
 static constexpr OlsVariant make_variant(const char *name) {
   OlsVariant v{};
   v.name = name;
@@ -454,16 +578,17 @@ static constexpr OlsVariant make_variant(const char *name) {
   v.G = G;
   v.nbuf = Gm::NBUF;
   v.precision = 0;
+  v.pair = PWPE > 0;
   v.lay.L = Gm::L;
   v.lay.T = Gm::T;
   v.lay.E = Gm::E;
   v.lay.P = Gm::P;
   for (int i = 0; i < kMaxStages; ++i) v.lay.R[i] = i < Gm::P ? Gm::R[i] : 1;
   v.lds_bytes = Gm::NBUF * G * Gm::LP * 8;
-  v.launch = &launch_variant<Gm, G, TWREG, PF, WPE>;
-  v.launch_batch = &launch_batch_variant<Gm, G, TWREG, PF, WPE>;
-  v.batch_blocks_per_cu = &batch_blocks_per_cu<Gm, G, TWREG, PF, WPE>;
-  v.grid_blocks_per_cu = &grid_blocks_per_cu<Gm, G, TWREG, PF, WPE>;
+  v.launch = &launch_variant<Gm, G, TWREG, PF, WPE, PWPE>;
+  v.launch_batch = &launch_batch_variant<Gm, G, TWREG, PF, WPE, PWPE>;
+  v.batch_blocks_per_cu = &batch_blocks_per_cu<Gm, G, TWREG, PF, WPE, PWPE>;
+  v.grid_blocks_per_cu = &grid_blocks_per_cu<Gm, G, TWREG, PF, WPE, PWPE>;
   return v;
 }
 
@@ -472,14 +597,15 @@ static constexpr OlsVariant make_variant(const char *name) {
 //       [_o<n>: registers capped for n waves per SIMD]
 static const OlsVariant kFp32Variants[] = {
     // the first entry for each length is the default for that length
-    make_variant<Geo<256, 32, 4, 8, 8>, 2, true, true, 4>("fp32_L256_t32x2_r4.8.8"),
+    make_variant<Geo<256, 32, 4, 8, 8>, 2, true, true, 4, 3>("fp32_L256_t32x2_r4.8.8"),
     make_variant<Geo<256, 16, 16, 16>, 4, true, true>("fp32_L256_t16x4_r16.16"),
-    make_variant<Geo<512, 64, 8, 8, 8>, 1, true, true, 4>("fp32_L512_t64_r8.8.8"),
+    make_variant<Geo<512, 64, 8, 8, 8>, 1, true, true, 4, 3>("fp32_L512_t64_r8.8.8"),
     make_variant<Geo<512, 32, 2, 16, 16>, 2, false, true>("fp32_L512_t32x2_r2.16.16_tg"),
+    make_variant<Geo<1024, 64, 4, 16, 16>, 1, true, true, 2, 2>("fp32_L1024_t64_r4.16.16_o2"),
     make_variant<Geo<1024, 128, 2, 8, 8, 8>, 1, true, true, 4>("fp32_L1024_t128_r2.8.8.8"),
     make_variant<Geo<1024, 64, 4, 16, 16>, 1, false, true>("fp32_L1024_t64_r4.16.16_tg"),
     make_variant<Geo<1024, 128, 2, 8, 8, 8>, 1, true, true, 3>("fp32_L1024_t128_r2.8.8.8_o3"),
-    make_variant<Geo<2048, 128, 8, 16, 16>, 1, true, true, 2>("fp32_L2048_t128_r8.16.16_o2"),
+    make_variant<Geo<2048, 128, 8, 16, 16>, 1, true, true, 2, 2>("fp32_L2048_t128_r8.16.16_o2"),
     make_variant<Geo<2048, 128, 8, 16, 16>, 1, true, false>("fp32_L2048_t128_r8.16.16_np"),
     make_variant<Geo<2048, 128, 8, 16, 16>, 1, false, true, 2>("fp32_L2048_t128_r8.16.16_tg_o2"),
     make_variant<Geo<2048, 256, 4, 8, 8, 8>, 1, true, true, 3>("fp32_L2048_t256_r4.8.8.8"),

@@ -1046,7 +1046,7 @@ static hipError_t launch_mixed4096_batch(const BatchArgs &a, hipStream_t st) {
 }
 
 template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
-static int mixed_batch_blocks_per_cu() {
+static int mixed_batch_blocks_per_cu(int) {
   if (!mixed_batch_persistent()) return 1;  // flat launch: the grid is the item count
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -1057,7 +1057,7 @@ static int mixed_batch_blocks_per_cu() {
 }
 
 template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
-static int mixed_grid_blocks_per_cu() {
+static int mixed_grid_blocks_per_cu(int) {
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
           &nb, reinterpret_cast<const void *>(&ols_mixed4096_kernel<H, PF, NT, NW, OCC, SPLIT, false>), 64 * NW,

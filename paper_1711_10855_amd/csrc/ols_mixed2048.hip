@@ -575,7 +575,7 @@ static hipError_t launch_batch(const BatchArgs &a, hipStream_t st) {
 }
 
 template <class H, bool NT, int OCC>
-static int batch_blocks_per_cu() {
+static int batch_blocks_per_cu(int) {
   if (!batch_persistent()) return 1;
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -586,7 +586,7 @@ static int batch_blocks_per_cu() {
 }
 
 template <class H, bool NT, int OCC>
-static int grid_blocks_per_cu() {
+static int grid_blocks_per_cu(int) {
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
           &nb, reinterpret_cast<const void *>(&ols_mixed2048_kernel<H, NT, OCC, false>), 64 * NW,

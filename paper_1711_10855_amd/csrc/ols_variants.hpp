@@ -66,7 +66,15 @@ struct OlsArgs {
   int bank_log2;     // mixed precision: the bank is stored times 2^bank_log2
   const void *consts;  // mixed precision: per-lane constants table
   CandOut cand;        // detection epilogue (count == nullptr: store the plane)
+  int pair;            // rows z and -z together (see unit_rows)
 };
+
+// What a work unit counts: rows, or in the pair form pairs of a row and its
+// mirror (z and -z, whose bank rows are complex conjugates; of an odd number
+// of rows the middle one stands alone).
+__host__ __device__ inline int unit_rows(int rows, bool pair) {
+  return pair ? (rows + 1) >> 1 : rows;
+}
 
 // One series of a batch as the persistent kernel sees it.
 struct SeriesDesc {
@@ -92,6 +100,7 @@ struct BatchArgs {
   int grid;             // persistent blocks
   int bank_log2;        // mixed precision: bank scale
   const void *consts;   // mixed precision: per-lane constants
+  int pair;             // as in OlsArgs
 };
 
 struct OlsVariant {
@@ -99,14 +108,15 @@ struct OlsVariant {
   int L, T, G, nbuf;
   int precision;     // FDAS_FP32 (0), FDAS_MIXED_FP16 (1), FDAS_MIXED_BF16 (2)
   int split;         // 1: hi + lo split products (FDAS_FLAG_SPLIT)
+  int pair;          // 1: has a pair form, used where the bank's rows mirror
   int zpb_target;    // > 0: templates per work unit fixed near this (balanced
                      // groups); 0: chosen per launch from the grid's rounds
   LayoutDesc lay;
   int lds_bytes;
   hipError_t (*launch)(const OlsArgs &, hipStream_t);
   hipError_t (*launch_batch)(const BatchArgs &, hipStream_t);
-  int (*batch_blocks_per_cu)();
-  int (*grid_blocks_per_cu)();  // occupancy of the single-spectrum kernel
+  int (*batch_blocks_per_cu)(int pair);
+  int (*grid_blocks_per_cu)(int pair);  // occupancy of the single-spectrum kernel
 };
 
 const OlsVariant *fp32_variants(int *count);

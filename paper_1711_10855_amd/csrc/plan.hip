@@ -41,6 +41,7 @@ struct fdas_plan_s {
   int cus = 0;
   bool zpb_forced = false;  // FDAS_ZPB or the autotuner fixed it
   int slots = 0;            // concurrently resident blocks of the grid kernel
+  int pair = 0;             // launches take rows z and -z together
   int last_zpb = 0;         // templates per unit of the last launch (a batch: its largest)
 };
 
@@ -369,6 +370,10 @@ static int build_plan_with(fdas_plan_t *out, const fdas_params &p, int nz, int d
   pl->L = p.seg_len;
   pl->U = p.seg_len - p.m;
   pl->var = var;
+  // Rows i and nz - 1 - i of the z grid are z and -z, whose templates are
+  // conjugate and even at integer offsets, so their bank rows are conjugates.
+  // At half-bin offsets the window [-m/2, m/2] is not even: no pairs there.
+  pl->pair = var->pair && !(p.flags & FDAS_FLAG_INTERBIN);
   pl->zpb = default_zpb(nz, var->zpb_target);
   if (const char *z = std::getenv("FDAS_ZPB")) {
     const int v = std::atoi(z);
@@ -479,20 +484,21 @@ static int launch_zpb(fdas_plan_t pl, int64_t nsb) {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device) != hipSuccess)
       return pl->zpb;
-    const int per = pl->var->grid_blocks_per_cu ? pl->var->grid_blocks_per_cu() : 0;
+    const int per = pl->var->grid_blocks_per_cu ? pl->var->grid_blocks_per_cu(pl->pair) : 0;
     if (per <= 0 || cus <= 0) return pl->zpb;
     pl->slots = cus * per;
   }
   double best = 0.0;
   int best_zpb = pl->zpb;
-  for (int ng = 1; ng <= std::min(pl->nz, 16); ++ng) {
-    const int zpb = (pl->nz + ng - 1) / ng;
-    const int groups = (pl->nz + zpb - 1) / zpb;
+  const int n = unit_rows(pl->nz, pl->pair), each = pl->pair ? 2 : 1;
+  for (int ng = 1; ng <= std::min(n, 16); ++ng) {
+    const int per = (n + ng - 1) / ng;
+    const int groups = (n + per - 1) / per;
     const double rounds = std::ceil((double)(nsb * groups) / (double)pl->slots);
-    const double cost = rounds * (zpb + 1.0);
+    const double cost = rounds * (each * per + 1.0);
     if (ng == 1 || cost < best * 0.999) {
       best = cost;
-      best_zpb = zpb;
+      best_zpb = std::min(each * per, pl->nz);
     }
   }
   // On grids of two or more full rounds, units of 40 templates with the
@@ -529,6 +535,7 @@ static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *p
   while ((1 << a.bank_log2) < pl->L) ++a.bank_log2;
   a.consts = pl->consts;
   a.cand = cand;
+  a.pair = pl->pair;
   hipError_t e = pl->var->launch(a, s);
   if (e != hipSuccess) return hip_error(e, "correlation kernel launch");
   return FDAS_OK;
@@ -593,7 +600,7 @@ static int batch_zpb(fdas_plan_t pl, int64_t nsb) {
   if (pl->zpb_forced) return pl->zpb;
   if (!pl->slots) {
     int cus = 0;
-    const int per = pl->var->grid_blocks_per_cu ? pl->var->grid_blocks_per_cu() : 0;
+    const int per = pl->var->grid_blocks_per_cu ? pl->var->grid_blocks_per_cu(pl->pair) : 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device) != hipSuccess ||
         per <= 0 || cus <= 0)
       return pl->zpb;
@@ -602,9 +609,10 @@ static int batch_zpb(fdas_plan_t pl, int64_t nsb) {
   return nsb >= 8 * (int64_t)pl->slots ? INT_MAX / 2 : pl->zpb;
 }
 
-static int64_t series_items(const SeriesDesc &d, int G) {
+static int64_t series_items(const SeriesDesc &d, int G, int pair) {
   const int64_t nsb = (d.nseg + G - 1) / G;
-  const int64_t nzg = (d.nz + d.zpb - 1) / d.zpb;
+  const int64_t per = unit_rows(d.zpb, pair);
+  const int64_t nzg = (unit_rows(d.nz, pair) + per - 1) / per;
   return nsb * nzg;
 }
 
@@ -616,7 +624,7 @@ static int batch_args(fdas_plan_t pl, const SeriesDesc *d_desc, int nseries, int
         hipDeviceGetAttribute(&pl->cus, hipDeviceAttributeMultiprocessorCount, pl->device);
     if (e != hipSuccess) return hip_error(e, "CU count");
   }
-  const int per_cu = std::max(1, pl->var->batch_blocks_per_cu());
+  const int per_cu = std::max(1, pl->var->batch_blocks_per_cu(pl->pair));
   a->desc = d_desc;
   a->nseries = nseries;
   a->total = total;
@@ -630,6 +638,7 @@ static int batch_args(fdas_plan_t pl, const SeriesDesc *d_desc, int nseries, int
   a->bank_log2 = 0;
   while ((1 << a->bank_log2) < pl->L) ++a->bank_log2;
   a->consts = pl->consts;
+  a->pair = pl->pair;
   return FDAS_OK;
 }
 
@@ -686,7 +695,7 @@ int plan_convolve_batch(fdas_plan_t pl, const fdas_series *series, int nseries, 
   for (int k = 0; k < nseries; ++k) {
     sorted[k] = desc[order[k]];
     sorted[k].item_begin = total;
-    total += series_items(sorted[k], G);
+    total += series_items(sorted[k], G, pl->pair);
   }
   if (total == 0) return FDAS_OK;
 
@@ -812,7 +821,7 @@ int plan_convolve_batch_noalloc(fdas_plan_t pl, const fdas_series *series, int n
     double c = 0.0;
     (void)series_desc(pl, series[order[k]], order[k], zpb, &d, &c);
     d.item_begin = total;
-    total += series_items(d, G);
+    total += series_items(d, G, pl->pair);
     if (++chunk.n == kDescChunk || k == nseries - 1) {
       const hipError_t e = launch_desc_upload(chunk, table, s);
       if (e != hipSuccess) return hip_error(e, "descriptor upload kernel");
