@@ -466,13 +466,16 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
   // 260 c + 16 n1 + 4 g (conflict-free 16-byte writes), and after the next
   // barrier wave w stores outputs [256 TPW w, 256 TPW (w + 1)) of the
   // segment, 1 KB contiguous per store instruction.
-  // A unit whose groups of 4 outputs lie wholly inside or wholly outside
-  // [half, half + U), below nbins and 16-byte aligned in every row stores one
-  // group per lane under a single predicate; others (the ragged last segment,
-  // rows not 16-byte aligned, odd m / 2) store element by element.
-  const bool vec_ok = half % 4 == 0 && ((int64_t)s * U - half) % 4 == 0 &&
-                      (int64_t)(s + 1) * U <= nbins && ld % 4 == 0 &&
-                      (reinterpret_cast<uintptr_t>(power_) & 15) == 0;
+  // A lane's group of 4 outputs that is kept whole goes out as one 16-byte
+  // store, which needs 4-byte alignment only, so any row stride and base
+  // will do; the groups that straddle an edge of the kept outputs (m / 2 not
+  // a multiple of 4, the ragged last segment) go value by value, on units
+  // that have any. (Storing every unit of rows not 16-byte aligned value by
+  // value took 158 us for 1048573 bins x 65 rows, against 78 us this way.)
+  const int64_t left_s = nbins - (int64_t)s * U;  // bins from segment output `half` on
+  const int nkeep = (int)(left_s < U ? left_s : U);
+  const bool edges = ((half | nkeep) & 3) != 0;
+  auto whole4 = [&](int o0) { return o0 >= half && o0 + 4 <= half + nkeep; };
   // The staged powers of the wave's TPW output blocks (one 16-byte LDS read
   // each), then their stores (or candidate offers).
   auto read_staged_from = [&](f4 *v, const float *sg) {
@@ -489,10 +492,9 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
   // path has at least one store after the bank row loaded before it.
   constexpr int kPast = (int)0x80000000u;
   // the 16-byte store's offset for each of the lane's groups (past the end
-  // unless the unit takes 16-byte stores and the group is kept), computed
-  // once per unit; through an empty asm statement, so that the store does
-  // not get split into copies under the unit's branch on vec_ok (every path
-  // must keep it, see below)
+  // unless the group is kept whole), computed once per unit; through an empty
+  // asm statement, so that the store does not get split into copies under a
+  // branch (every path must keep it, see below)
   // (PF == 7; PF == 5 computes it at the store, which measured faster there;
   // PF == 8 stores from the stage-0' lanes, whose group of tile
   // n1 = TPW w + q starts at output 256 c + 16 n1 + 4 g)
@@ -501,14 +503,12 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
       const int o0 = PF == 7 ? 256 * (TPW * w + q) + 4 * lane : 256 * c + 16 * (TPW * w + q) + 4 * g;
-      off4[q] = vec_ok && o0 >= half && o0 < half + U ? (o0 - half) * 4 : kPast;
+      off4[q] = whole4(o0) ? (o0 - half) * 4 : kPast;
       asm volatile("" : "+v"(off4[q]));
     }
   }
   auto write_staged_buffer = [&](int izr, const f4 *vv, bool none) {
     const int64_t rbase = (int64_t)s * U;  // plane column of segment output `half`
-    const int64_t left = nbins - rbase;
-    const int nkeep = (int)(left < U ? left : U);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         power_ + (int64_t)(izr - row_base) * ld + rbase, (short)0, nkeep * 4, 0x00020000);
     constexpr int aux = NT ? 2 : 0;  // nontemporal
@@ -519,15 +519,14 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
       if constexpr (PF == 7) {
         off = none ? kPast : off4[q];
       } else {
-        const bool keep4 = !none && vec_ok && o0 >= half && o0 < half + U;
-        off = keep4 ? (o0 - half) * 4 : kPast;
+        off = !none && whole4(o0) ? (o0 - half) * 4 : kPast;
       }
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, vv[q]), rs, off, 0, aux);
-      if (!vec_ok && !none) {
+      if (edges && !none) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int o = o0 + i;
-          const bool keep = !none && o >= half && o < half + U && o - half < nkeep;
+          const bool keep = !whole4(o0) && o >= half && o < half + nkeep;
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(vv[q][i]), rs,
                                                 keep ? (o - half) * 4 : kPast, 0, aux);
         }
@@ -540,8 +539,6 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
   // (tile n1 + 1) writes the other half of each 128-byte line.
   auto write_direct = [&](int izr, const f4 *vv, bool none) {
     const int64_t rbase = (int64_t)s * U;
-    const int64_t left = nbins - rbase;
-    const int nkeep = (int)(left < U ? left : U);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         power_ + (int64_t)(izr - row_base) * ld + rbase, (short)0, nkeep * 4, 0x00020000);
     constexpr int aux = NT ? 2 : 0;  // nontemporal
@@ -550,11 +547,11 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
       const int o0 = 256 * c + 16 * (TPW * w + q) + 4 * g;
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, vv[q]), rs,
                                              none ? kPast : off4[q], 0, aux);
-      if (!vec_ok && !none) {
+      if (edges && !none) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int o = o0 + i;
-          const bool keep = o >= half && o < half + U && o - half < nkeep;
+          const bool keep = !whole4(o0) && o >= half && o < half + nkeep;
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(vv[q][i]), rs,
                                                 keep ? (o - half) * 4 : kPast, 0, aux);
         }
@@ -580,16 +577,16 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
         offer4(cd, v, active, o0, half, U, r0, nbins, izr - row_base);
         continue;
       }
-      if (vec_ok) {
-        if (o0 >= half && o0 < half + U) {
-          if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<gptr<f4>>(prow + r0));
-          else *reinterpret_cast<gptr<f4>>(prow + r0) = v;
-        }
-      } else {
+      const auto dst = prow + r0;
+      if (whole4(o0)) {
+        typedef f4 __attribute__((aligned(4))) f4u;
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<gptr<f4u>>(dst));
+        else *reinterpret_cast<gptr<f4u>>(dst) = v;
+      } else if (edges) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int o = o0 + i;
-          if (o >= half && o < half + U && r0 + i < nbins) prow[r0 + i] = v[i];
+          if (o >= half && o < half + nkeep) dst[i] = v[i];
         }
       }
     }

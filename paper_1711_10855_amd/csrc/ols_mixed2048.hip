@@ -329,11 +329,13 @@ __device__ __forceinline__ void unit2048(const unsigned char *__restrict__ const
   // Stores: wave w writes outputs [256 w, 256 w + 256), a lane four
   // consecutive ones (1 KB per store instruction), gathered from the
   // [n2][n0][n1] staging.
-  const bool vec_ok = half % 4 == 0 && ((int64_t)s * U - half) % 4 == 0 &&
-                      (int64_t)(s + 1) * U <= nbins && ld % 4 == 0 &&
-                      (reinterpret_cast<uintptr_t>(power_) & 15) == 0;
+  // A group kept whole is one 16-byte store, which needs 4-byte alignment
+  // only; groups that straddle an edge of the kept outputs go value by value.
+  const int64_t left_s = nbins - (int64_t)s * U;  // bins from segment output `half` on
+  const int nkeep = (int)(left_s < U ? left_s : U);
   const int o0 = 256 * w + 4 * lane;
   const int sgi = kStgN2 * (o0 & 7) + kStgN0 * (o0 >> 7) + ((o0 >> 3) & 15);
+  const bool whole4 = o0 >= half && o0 + 4 <= half + nkeep;
   const int64_t r0 = (int64_t)s * U + o0 - half;
   auto gather = [&](int b) {
     const float *sb = stg + b * kStg + sgi;
@@ -352,18 +354,14 @@ __device__ __forceinline__ void unit2048(const unsigned char *__restrict__ const
       return;
     }
     const auto dst = prow + r0;
-    if (vec_ok) {
-      if (o0 >= half && o0 < half + U) {
-        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<gptr<f4>>(dst));
-        else *reinterpret_cast<gptr<f4>>(dst) = v;
-      }
-    } else {
-      // ragged segment: outputs inside [half, half + U) and below nbins
-      const int64_t left = nbins - r0;
-      const int lim = (int)(left < 4 ? (left < 0 ? 0 : left) : 4);
+    if (whole4) {
+      typedef f4 __attribute__((aligned(4))) f4u;
+      if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<gptr<f4u>>(dst));
+      else *reinterpret_cast<gptr<f4u>>(dst) = v;
+    } else if (((half | nkeep) & 3) != 0) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (i < lim && o0 + i >= half && o0 + i < half + U) dst[i] = v[i];
+        if (o0 + i >= half && o0 + i < half + nkeep) dst[i] = v[i];
     }
   };
 

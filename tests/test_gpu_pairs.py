@@ -1,6 +1,7 @@
 """Rows z and -z taken together (one bank row for both): numbers of rows with
-and without a middle row, unit sizes that leave remainders, and series of a
-batch with fewer drifts than the plan, against the FP64 oracle."""
+and without a middle row, unit sizes that leave remainders, rows of no
+alignment, and series of a batch with fewer drifts than the plan, against the
+FP64 oracle."""
 
 import numpy as np
 import pytest
@@ -10,10 +11,13 @@ from paper_1711_10855_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# the bars of the precisions: plain FP32 and the hi+lo split 1e-4 / 1e-3 of the
-# largest power, as for every other plane
+# the bars of the precisions, as for every other plane: 1e-4 of the largest
+# power in plain FP32, 1e-3 on the matrix cores (flag 1: hi+lo split). The
+# widths give m / 2 both a multiple of 4 and not, the row strides no alignment.
 FORMS = [("fp32", 256, 64, 0, 1e-4), ("fp32", 512, 64, 0, 1e-4), ("fp32", 1024, 128, 0, 1e-4),
-         ("fp32", 2048, 256, 0, 1e-4)]
+         ("fp32", 2048, 256, 0, 1e-4), ("fp16", 4096, 256, 0, 1e-3), ("fp16", 4096, 50, 0, 1e-3),
+         ("fp16", 4096, 128, 1, 1e-3), ("bf16", 4096, 60, 1, 1e-3), ("fp16", 2048, 64, 0, 1e-3),
+         ("fp16", 2048, 54, 0, 1e-3)]
 
 
 def to_dev(a):
