@@ -249,7 +249,7 @@ int fdas_make_templates(const fdas_params *p, void *templates, size_t *bytes, vo
   hipError_t e = hipMalloc(&h, (size_t)nz * (size_t)(r.m + 1) * 16);
   if (e != hipSuccess) return set_error(FDAS_ERR_NOMEM, "template temporary: %s", hipGetErrorString(e));
   e = launch_templates(h, nz, r.m, r.zmax, r.dz, interbin, s);
-  if (e == hipSuccess) e = launch_bank(static_cast<c32 *>(templates), h, nz, r.m, nat, s);
+  if (e == hipSuccess) e = launch_bank(static_cast<c32 *>(templates), h, nz, interbin, r.m, nat, s);
   const hipError_t e2 = hipStreamSynchronize(s);
   (void)hipFree(h);
   if (e != hipSuccess) return hip_error(e, "bank kernel launch");

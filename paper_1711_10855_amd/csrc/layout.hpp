@@ -48,4 +48,17 @@ __host__ __device__ inline int layout_slot_freq(const LayoutDesc &d, int t, int 
   return k;
 }
 
+// Bank index e T + t of the slot that holds frequency k (the inverse of
+// layout_slot_freq).
+__host__ __device__ inline int layout_freq_slot(const LayoutDesc &d, int k) {
+  int a = 0;
+  for (int i = 0; i < d.P; ++i) {
+    a += (k % d.R[i]) * layout_stride(d, i);
+    k /= d.R[i];
+  }
+  const int r = d.R[d.P - 1];
+  const int b = a / r, n = a % r;
+  return ((b / d.T) * r + n) * d.T + b % d.T;
+}
+
 }  // namespace fdas

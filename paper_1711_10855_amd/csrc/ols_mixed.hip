@@ -44,6 +44,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "bank_sum.hpp"
 #include "fft_radix.hpp"
 #include "cand4.hpp"
 #include "ols_variants.hpp"
@@ -1138,10 +1139,6 @@ const OlsVariant *mixed_variants(int *count) {
 // 2^bank_log2 = L from the power). Planes: Re, Im, rounded to 16 bits, or
 // with split to FP32 (the split kernel forms the product in FP32 and splits
 // it; the same 8 bytes per value as 16-bit hi and lo planes).
-struct c64m {
-  double x, y;
-};
-
 __device__ __forceinline__ int bank_slot_k(int slot) {
   const int row = slot >> 4;
   const int k2 = (slot & 15) ^ (((row >> 7) & 1) << 2);
@@ -1155,36 +1152,28 @@ __device__ __forceinline__ void put_split(H *hi, H *lo, double v) {
   if (lo) *lo = (H)(v - (double)(float)a);
 }
 
-template <class H>
-__global__ void bank_mixed_kernel(H *__restrict__ bank, const c64m *__restrict__ h, int nz, int m,
-                                  int L, int split) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long)nz * L) return;
-  const int i = (int)(idx / L);
-  const int slot = (int)(idx % L);
-  const int k = bank_slot_k(slot);
-  const c64m *hi = h + (long)i * (m + 1);
-  double sr = 0.0, si = 0.0;
-  for (int j = 0; j <= m; ++j) {
-    const int q = j - m / 2;
-    const int qm = ((q % L) + L) % L;
-    const long ph = ((long)qm * k) % L;
-    double sn, cs;
-    sincospi(-2.0 * (double)ph / (double)L, &sn, &cs);
-    const c64m v = hi[j];
-    sr += v.x * cs - v.y * sn;
-    si += v.x * sn + v.y * cs;
-  }
-  if (split) {
-    float *row_f = reinterpret_cast<float *>(bank) + (long)i * 2 * L;
-    row_f[slot] = (float)sr;       // Re T'
-    row_f[L + slot] = (float)-si;  // Im T'
-    return;
-  }
-  H *row_i = bank + (long)i * 2 * L;
-  row_i[slot] = (H)sr;       // Re T'
-  row_i[L + slot] = (H)-si;  // Im T'
+__device__ __forceinline__ int bank_k_slot(int k) {  // the inverse
+  const int row = 16 * (k & 15) + ((k >> 4) & 15);
+  return row * 16 + ((k >> 8) ^ (((row >> 7) & 1) << 2));
 }
+
+template <class H, bool SPLIT>
+struct PutMixed {
+  H *bank;
+  int L;
+  __device__ void operator()(int row, int k, double re, double im) const {
+    const int slot = bank_k_slot(k);
+    if constexpr (SPLIT) {
+      float *row_f = reinterpret_cast<float *>(bank) + (long)row * 2 * L;
+      row_f[slot] = (float)re;       // Re T'
+      row_f[L + slot] = (float)-im;  // Im T'
+    } else {
+      H *row_h = bank + (long)row * 2 * L;
+      row_h[slot] = (H)re;
+      row_h[L + slot] = (H)-im;
+    }
+  }
+};
 
 template <class H>
 __global__ void bank_mixed_natural_kernel(c32 *__restrict__ dst, const H *__restrict__ bank,
@@ -1251,20 +1240,21 @@ hipError_t launch_mixed_consts(void *out, int L, int precision, int split, hipSt
   return hipGetLastError();
 }
 
-hipError_t launch_bank_mixed(void *bank, const void *h, int nz, int m, int L, int precision,
-                             int split, hipStream_t s) {
+template <class H>
+static hipError_t launch_bank_mixed_as(void *bank, const void *h, int rows, int interbin, int m,
+                                       int L, int split, hipStream_t s) {
+  H *b = static_cast<H *>(bank);
+  return split ? launch_bank_sum(h, rows, interbin, m, L, PutMixed<H, true>{b, L}, s)
+               : launch_bank_sum(h, rows, interbin, m, L, PutMixed<H, false>{b, L}, s);
+}
+
+hipError_t launch_bank_mixed(void *bank, const void *h, int rows, int interbin, int m, int L,
+                             int precision, int split, hipStream_t s) {
   if (L == 2048)
-    return split ? hipErrorInvalidValue : launch_bank_mixed2048(bank, h, nz, m, precision, s);
-  const long n = (long)nz * L;
-  const dim3 grid((unsigned)((n + 255) / 256));
-  if (precision == 2)
-    hipLaunchKernelGGL(bank_mixed_kernel<__bf16>, grid, dim3(256), 0, s,
-                       static_cast<__bf16 *>(bank), static_cast<const c64m *>(h), nz, m, L, split);
-  else
-    hipLaunchKernelGGL(bank_mixed_kernel<_Float16>, grid, dim3(256), 0, s,
-                       static_cast<_Float16 *>(bank), static_cast<const c64m *>(h), nz, m, L,
-                       split);
-  return hipGetLastError();
+    return split ? hipErrorInvalidValue
+                 : launch_bank_mixed2048(bank, h, rows, interbin, m, precision, s);
+  return precision == 2 ? launch_bank_mixed_as<__bf16>(bank, h, rows, interbin, m, L, split, s)
+                        : launch_bank_mixed_as<_Float16>(bank, h, rows, interbin, m, L, split, s);
 }
 
 hipError_t launch_bank_mixed_natural(c32 *dst, const void *bank, int nz, int L, int precision,

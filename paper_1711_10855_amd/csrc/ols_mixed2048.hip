@@ -42,6 +42,7 @@
 
 #include <cstdint>
 
+#include "bank_sum.hpp"
 #include "fft_radix.hpp"
 #include "cand4.hpp"
 #include "ols_variants.hpp"
@@ -621,36 +622,21 @@ static OlsVariant make(const char *name, int precision) {
 }
 
 // ---- plan-time tables ------------------------------------------------------
-struct c64m {
-  double x, y;
-};
 
-// bank[i][plane][(k0 16 + k1) 8 + k2] = conj(FFT_L(h_i))[k0 + 16 k1 + 256 k2]
-// (no 1/L; the kernel removes the factor 2^bank_log2 = L from the power);
-// planes Re, Im rounded to 16 bits.
+// ---- plan-time: planar bank ------------------------------------------------
+// bank[row][Re | Im][8 (16 k0 + k1) + k2] for frequency k = k0 + 16 k1 +
+// 256 k2: conj(S)[k] in 16 bits (no 1/L; the kernel removes the factor
+// 2^bank_log2 = L from the power).
 template <class H>
-__global__ void bank_kernel(H *__restrict__ bank, const c64m *__restrict__ h, int nz, int m) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long)nz * L) return;
-  const int i = (int)(idx / L);
-  const int slot = (int)(idx % L);
-  const int k = (slot >> 7) + 16 * ((slot >> 3) & 15) + 256 * (slot & 7);
-  const c64m *hi = h + (long)i * (m + 1);
-  double sr = 0.0, si = 0.0;
-  for (int j = 0; j <= m; ++j) {
-    const int q = j - m / 2;
-    const int qm = ((q % L) + L) % L;
-    const long ph = ((long)qm * k) % L;
-    double sn, cs;
-    sincospi(-2.0 * (double)ph / (double)L, &sn, &cs);
-    const c64m v = hi[j];
-    sr += v.x * cs - v.y * sn;
-    si += v.x * sn + v.y * cs;
+struct PutPlanes {
+  H *bank;
+  __device__ void operator()(int row, int k, double re, double im) const {
+    const int slot = 8 * (16 * (k & 15) + ((k >> 4) & 15)) + (k >> 8);
+    H *row_h = bank + (long)row * 2 * L;
+    row_h[slot] = (H)re;
+    row_h[L + slot] = (H)(-im);
   }
-  H *row_i = bank + (long)i * 2 * L;
-  row_i[slot] = (H)sr;
-  row_i[L + slot] = (H)(-si);
-}
+};
 
 template <class H>
 __global__ void bank_natural_kernel(c32 *__restrict__ dst, const H *__restrict__ bank, int nz) {
@@ -753,17 +739,13 @@ hipError_t launch_mixed2048_consts(void *out, int precision, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_bank_mixed2048(void *bank, const void *h, int nz, int m, int precision,
-                                 hipStream_t s) {
-  const long n = (long)nz * m2048::L;
-  const dim3 grid((unsigned)((n + 255) / 256));
-  if (precision == 2)
-    hipLaunchKernelGGL(m2048::bank_kernel<__bf16>, grid, dim3(256), 0, s,
-                       static_cast<__bf16 *>(bank), static_cast<const m2048::c64m *>(h), nz, m);
-  else
-    hipLaunchKernelGGL(m2048::bank_kernel<_Float16>, grid, dim3(256), 0, s,
-                       static_cast<_Float16 *>(bank), static_cast<const m2048::c64m *>(h), nz, m);
-  return hipGetLastError();
+hipError_t launch_bank_mixed2048(void *bank, const void *h, int rows, int interbin, int m,
+                                 int precision, hipStream_t s) {
+  return precision == 2
+             ? launch_bank_sum(h, rows, interbin, m, m2048::L,
+                               m2048::PutPlanes<__bf16>{static_cast<__bf16 *>(bank)}, s)
+             : launch_bank_sum(h, rows, interbin, m, m2048::L,
+                               m2048::PutPlanes<_Float16>{static_cast<_Float16 *>(bank)}, s);
 }
 
 hipError_t launch_bank_mixed2048_natural(c32 *dst, const void *bank, int nz, int precision,

@@ -121,8 +121,9 @@ struct OlsVariant {
 
 const OlsVariant *fp32_variants(int *count);
 const OlsVariant *mixed_variants(int *count);
-hipError_t launch_bank_mixed(void *bank, const void *h, int nz, int m, int L, int precision,
-                             int split, hipStream_t s);
+// (rows: bank rows; interbin: every second one at half-bin offsets)
+hipError_t launch_bank_mixed(void *bank, const void *h, int rows, int interbin, int m, int L,
+                             int precision, int split, hipStream_t s);
 size_t mixed_consts_bytes(int L, int split);
 hipError_t launch_mixed_consts(void *out, int L, int precision, int split, hipStream_t s);
 hipError_t launch_bank_mixed_natural(c32 *dst, const void *bank, int nz, int L, int precision,
@@ -132,8 +133,8 @@ hipError_t launch_bank_mixed_natural(c32 *dst, const void *bank, int nz, int L, 
 const OlsVariant *mixed2048_variants(int *count);
 size_t mixed2048_consts_bytes();
 hipError_t launch_mixed2048_consts(void *out, int precision, hipStream_t s);
-hipError_t launch_bank_mixed2048(void *bank, const void *h, int nz, int m, int precision,
-                                 hipStream_t s);
+hipError_t launch_bank_mixed2048(void *bank, const void *h, int rows, int interbin, int m,
+                                 int precision, hipStream_t s);
 hipError_t launch_bank_mixed2048_natural(c32 *dst, const void *bank, int nz, int precision,
                                          hipStream_t s);
 
@@ -141,8 +142,8 @@ hipError_t launch_reset_counter(unsigned long long *counter, hipStream_t s);
 hipError_t launch_templates(void *out, int rows, int m, double zmax, double dz, int interbin,
                             hipStream_t s);
 hipError_t launch_twiddles(c32 *tw, int L, hipStream_t s);
-hipError_t launch_bank(c32 *bank, const void *h, int nz, int m, const LayoutDesc &lay,
-                       hipStream_t s);
+hipError_t launch_bank(c32 *bank, const void *h, int rows, int interbin, int m,
+                       const LayoutDesc &lay, hipStream_t s);
 hipError_t launch_bank_natural(c32 *dst, const c32 *bank, int nz,
                                const LayoutDesc &lay, hipStream_t s);
 

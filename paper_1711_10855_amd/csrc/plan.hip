@@ -402,12 +402,13 @@ static int build_plan_with(fdas_plan_t *out, const fdas_params &p, int nz, int d
     destroy_plan(pl);
     return set_error(FDAS_ERR_NOMEM, "plan allocation: %s", hipGetErrorString(e));
   }
-  e = launch_templates(h, nz, p.m, p.zmax, p.dz, (p.flags & FDAS_FLAG_INTERBIN) ? 1 : 0, s);
+  const int interbin = (p.flags & FDAS_FLAG_INTERBIN) ? 1 : 0;
+  e = launch_templates(h, nz, p.m, p.zmax, p.dz, interbin, s);
   if (e == hipSuccess) {
     if (p.precision == FDAS_FP32)
-      e = launch_bank(static_cast<c32 *>(pl->bank), h, nz, p.m, var->lay, s);
+      e = launch_bank(static_cast<c32 *>(pl->bank), h, nz, interbin, p.m, var->lay, s);
     else
-      e = launch_bank_mixed(pl->bank, h, nz, p.m, p.seg_len, p.precision, split, s);
+      e = launch_bank_mixed(pl->bank, h, nz, interbin, p.m, p.seg_len, p.precision, split, s);
   }
   if (e == hipSuccess) e = launch_twiddles(static_cast<c32 *>(pl->tw), p.seg_len, s);
   if (e == hipSuccess && pl->consts)
