@@ -272,14 +272,15 @@ __device__ __forceinline__ void load_mixed_consts(MixedConsts<H, NW, SPLIT> &K,
 
 // One work unit of the mixed kernel: segment s, bank rows [z0, z1), plane
 // rows iz - row_base. Every thread of the block calls it (barriers inside).
-template <class H, int PF, bool NT, int NW, bool SPLIT, bool CAND>
+template <class H, int PF, bool NT, int NW, bool SPLIT, bool CAND, bool PAIR>
 __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ consts_,
                                            const c32 *__restrict__ spec_, int64_t nbins,
                                            const H *__restrict__ bank_, const c32 *__restrict__ tw_,
                                            float *__restrict__ power_, int64_t ld, int s,
                                            bool active, int U, int half, int z0, int z1,
-                                           int row_base, int bank_log2, unsigned char *smem,
-                                           float *s_max, const CandOut &cd, int t_in = -1) {
+                                           int row_base, int rows, int bank_log2,
+                                           unsigned char *smem, float *s_max, const CandOut &cd,
+                                           int t_in = -1) {
   typedef typename Vec<H>::v8 v8;
   constexpr int L = 4096;
   constexpr int TPW = 16 / NW;
@@ -599,7 +600,17 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
   };
 
   // ---- product + stage 2' (tiles k0 = TPW w + j; rows k1 = c; chunk h) ----
-  auto product_stage2_to = [&](H *ea) {
+  // With `conj` (the mirror row, whose bank row is the conjugate) Im T changes
+  // its sign: the second product's on the lanes that form Re Y, the first's
+  // on the others. Split: the sign goes into the lane's X (FP32, by `flip`);
+  // else the other lanes take the same difference and change the sign of the
+  // packed result. Either way every bit is that of the mirror's own row.
+  const unsigned flip = re_lane ? 0u : (SPLIT ? ~0u : 0x80008000u);
+  auto flip_f = [](float v, unsigned mask) {
+    return __uint_as_float(__float_as_uint(v) ^ (mask & 0x80000000u));
+  };
+  auto product_stage2_to = [&](H *ea, auto conjc) {
+    constexpr bool conj = decltype(conjc)::value;
     v8 av[TPW], avl[SPLIT ? TPW : 1];
 #pragma unroll
     for (int j = 0; j < TPW; ++j) {
@@ -610,7 +621,12 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
         for (int i = 0; i < 8; ++i) {
           const float tr = sbr[2 * j + (i >> 2)][i & 3];
           const float ti = sbi[2 * j + (i >> 2)][i & 3];
-          y[i] = __builtin_fmaf(xrf[j][i], tr, xif[j][i] * ti);
+          const float a = conj ? flip_f(xrf[j][i], flip) : xrf[j][i];
+          const float b = conj ? flip_f(xif[j][i], ~flip) : xif[j][i];
+          y[i] = __builtin_fmaf(a, tr, b * ti);
+          // (opaque, or the compiler forms FP16 hi values by a second, mixed
+          // precision multiply-add per value, and not in every form)
+          if constexpr (std::is_same<H, _Float16>::value) asm("" : "+v"(y[i]));
         }
         u32x4 hi, lo;
 #pragma unroll
@@ -622,7 +638,20 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
         av[j] = __builtin_bit_cast(v8, hi);
         avl[j] = __builtin_bit_cast(v8, lo);
       } else {
-        av[j] = xr[j] * btr[j] + xi[j] * bti[j];
+        // (FP16: the fused form spelled out, so that every form of the kernel
+        // rounds alike)
+        if constexpr (std::is_same<H, _Float16>::value) {
+          const v8 p = xi[j] * bti[j];
+          av[j] = __builtin_elementwise_fma(xr[j], btr[j], conj ? -p : p);
+          if constexpr (conj) {
+            const u32x4 d = __builtin_bit_cast(u32x4, av[j]);
+            av[j] = __builtin_bit_cast(
+                v8, u32x4{d[0] ^ flip, d[1] ^ flip, d[2] ^ flip, d[3] ^ flip});
+          }
+        } else {
+          static_assert(!conj, "no unsplit BF16 variant has a pair form");
+          av[j] = xr[j] * btr[j] + xi[j] * bti[j];
+        }
       }
     }
 #pragma unroll
@@ -634,7 +663,7 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
       store_stage<H, SPLIT>(ea, 16 * c + k0, g, dr, di);  // stage 1' butterfly (k0, n2 = c)
     }
   };
-  auto product_stage2 = [&]() { product_stage2_to(Ea); };
+  auto product_stage2 = [&]() { product_stage2_to(Ea, std::false_type{}); };
   // ---- stage 1' (tiles n2 = TPW w + j; rows k0 = c) -------------------------
   auto stage1_from = [&](const H *ea, H *eb) {
 #pragma unroll
@@ -749,7 +778,7 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
         read_staged_from(vv, sg_r);
         if (s1v) stage1_from(ea_r, eb_w);
         if (s0v) stage0_from(eb_r, sg_w);
-        if (s2v) product_stage2_to(ea_w);
+        if (s2v) product_stage2_to(ea_w, std::false_type{});
         load_bank(z0 + (k + 1 < n ? k + 1 : n - 1));
         write_staged_buffer(stv ? z0 + k - 3 : z0, vv, !stv);
         __syncthreads();
@@ -809,7 +838,7 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
 #pragma unroll
           for (int q = 0; q < TPW; ++q) vv[q] = __builtin_bit_cast(f4, K.q1[0]);
         }
-        if (s2v) product_stage2_to(ea_w);
+        if (s2v) product_stage2_to(ea_w, std::false_type{});
         load_bank(z0 + (k + 1 < n ? k + 1 : n - 1));
         write_direct(s0v ? z0 + k - 2 : z0, vv, !s0v);
         __syncthreads();
@@ -835,6 +864,45 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
         if (k & 1) phase(k, p1, s2v, s1v, true);
         else phase(k, p0, s2v, s1v, true);
       }
+    }
+  } else if constexpr (PAIR) {
+    // The PF == 5 schedule over pairs of a row and its mirror: one bank row
+    // is loaded for both, right after the mirror's product has read it. The
+    // bank rows' loads cost 6 of 43 ms on the wide batch (without any: 37 ms);
+    // half of them gives 188.7 -> 179.0 us on 2^21 bins x 101 rows and 2899 ->
+    // 2797 us on 8 series of 2^21 bins x 201 rows (FP16), and 202 -> 195 us
+    // on 2^20 bins x 101 rows (split BF16, whose bank row is 64 bytes a lane).
+    static_assert(PF == 5 && !CAND, "the pair form is that of PF == 5");
+    if (z0 < z1 && active) {
+      const int mirror = 2 * row_base + rows - 1;
+      load_bank(z0);
+      f4 v[TPW];
+#pragma unroll
+      for (int q = 0; q < TPW; ++q) v[q] = __builtin_bit_cast(f4, K.q1[0]);  // any live value: nothing is written
+      write_staged_buffer(z0, v, true);
+      int prev = z0;  // the row whose powers are staged
+      for (int iz = z0; iz < z1; ++iz) {
+        product_stage2();
+        __syncthreads();
+        stage1();
+        read_staged(v);
+        write_staged_buffer(prev, v, iz == z0);
+        __syncthreads();
+        stage0();
+        prev = iz;
+        if (mirror - iz == iz) break;  // the middle row (z = 0) comes last and alone
+        product_stage2_to(Ea, std::true_type{});
+        load_bank(iz + 1 < z1 ? iz + 1 : iz);
+        __syncthreads();
+        stage1();
+        read_staged(v);
+        write_staged_buffer(prev, v, false);
+        __syncthreads();
+        stage0();
+        prev = mirror - iz;
+      }
+      __syncthreads();
+      store_staged(prev);
     }
   } else if constexpr (PF == 5 && !CAND) {
     if (z0 < z1 && active) {
@@ -906,7 +974,7 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
   }
 }
 
-template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT, bool CAND>
+template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT, bool CAND, bool PAIR>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
     ols_mixed4096_kernel(const c32 *__restrict__ spec, int64_t nbins, const H *__restrict__ bank,
                          const c32 *__restrict__ tw, const unsigned char *__restrict__ consts,
@@ -917,9 +985,10 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OC
   const int sb = blockIdx.x % nsb;
   const int zg = blockIdx.x / nsb;
   const int z0 = zg * zpb;
-  const int z1 = min(nz, z0 + zpb);
-  mixed_unit<H, PF, NT, NW, SPLIT, CAND>(consts, spec, nbins, bank, tw, power, ld, sb, sb < nseg,
-                                         U, half, z0, z1, 0, bank_log2, smem, s_max, cand);
+  const int z1 = min(unit_rows(nz, PAIR), z0 + zpb);
+  mixed_unit<H, PF, NT, NW, SPLIT, CAND, PAIR>(consts, spec, nbins, bank, tw, power, ld, sb,
+                                               sb < nseg, U, half, z0, z1, 0, nz, bank_log2, smem,
+                                               s_max, cand);
 }
 
 // Batched form as one flat launch: block b takes work item b (items are
@@ -927,7 +996,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OC
 // dispatcher hands out items in that order as blocks retire. Same body as
 // the single-series kernel (FDAS_BATCH_PERSISTENT=0; the persistent form
 // below is the default).
-template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
+template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT, bool PAIR>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
     ols_mixed4096_items_kernel(const SeriesDesc *__restrict__ desc, int nseries,
                                const H *__restrict__ bank, const c32 *__restrict__ tw,
@@ -946,38 +1015,42 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OC
   const long long local = item - d.item_begin;
   const int zg = (int)(local / d.nseg);
   const int sb = (int)(local % d.nseg);
-  const int z0 = d.row_off + zg * d.zpb;
-  const int z1 = min(d.row_off + d.nz, z0 + d.zpb);
+  const int per = unit_rows(d.zpb, PAIR);
+  const int z0 = d.row_off + zg * per;
+  const int z1 = min(d.row_off + unit_rows(d.nz, PAIR), z0 + per);
   const CandOut none{};
-  mixed_unit<H, PF, NT, NW, SPLIT, false>(consts, static_cast<const c32 *>(d.spec), d.nbins, bank, tw, d.power,
-                            d.ld, sb, true, U, half, z0, z1, d.row_off, bank_log2, smem, s_max,
-                            none);
+  mixed_unit<H, PF, NT, NW, SPLIT, false, PAIR>(consts, static_cast<const c32 *>(d.spec), d.nbins,
+                                                bank, tw, d.power, d.ld, sb, true, U, half, z0, z1,
+                                                d.row_off, d.nz, bank_log2, smem, s_max, none);
+}
+
+template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT, bool CAND, bool PAIR>
+static hipError_t launch_mixed4096_form(const OlsArgs &a, hipStream_t st) {
+  const int nsb = a.nseg;
+  const int per = unit_rows(a.zpb, PAIR);
+  const int nzg = (unit_rows(a.nz, PAIR) + per - 1) / per;
+  const long blocks = (long)nsb * nzg;
+  hipLaunchKernelGGL((ols_mixed4096_kernel<H, PF, NT, NW, OCC, SPLIT, CAND, PAIR>),
+                     dim3((unsigned)blocks), dim3(64 * NW), 0, st,
+                     static_cast<const c32 *>(a.spec), a.nbins, static_cast<const H *>(a.bank),
+                     static_cast<const c32 *>(a.tw), static_cast<const unsigned char *>(a.consts),
+                     a.power, a.ld, a.nseg, a.U, a.half, a.nz, per, nsb, a.bank_log2, a.cand);
+  return hipGetLastError();
 }
 
 template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
 static hipError_t launch_mixed4096(const OlsArgs &a, hipStream_t st) {
-  const int nsb = a.nseg;
-  const int nzg = (a.nz + a.zpb - 1) / a.zpb;
-  const long blocks = (long)nsb * nzg;
-  if (a.cand.count)
-    hipLaunchKernelGGL((ols_mixed4096_kernel<H, PF, NT, NW, OCC, SPLIT, true>), dim3((unsigned)blocks),
-                       dim3(64 * NW), 0, st, static_cast<const c32 *>(a.spec), a.nbins,
-                       static_cast<const H *>(a.bank), static_cast<const c32 *>(a.tw),
-                       static_cast<const unsigned char *>(a.consts), a.power, a.ld, a.nseg, a.U,
-                       a.half, a.nz, a.zpb, nsb, a.bank_log2, a.cand);
-  else
-    hipLaunchKernelGGL((ols_mixed4096_kernel<H, PF, NT, NW, OCC, SPLIT, false>), dim3((unsigned)blocks),
-                       dim3(64 * NW), 0, st, static_cast<const c32 *>(a.spec), a.nbins,
-                       static_cast<const H *>(a.bank), static_cast<const c32 *>(a.tw),
-                       static_cast<const unsigned char *>(a.consts), a.power, a.ld, a.nseg, a.U,
-                       a.half, a.nz, a.zpb, nsb, a.bank_log2, a.cand);
-  return hipGetLastError();
+  if (a.cand.count) return launch_mixed4096_form<H, PF, NT, NW, OCC, SPLIT, true, false>(a, st);
+  if constexpr (PF == 5) {
+    if (a.pair) return launch_mixed4096_form<H, PF, NT, NW, OCC, SPLIT, false, true>(a, st);
+  }
+  return launch_mixed4096_form<H, PF, NT, NW, OCC, SPLIT, false, false>(a, st);
 }
 
 // Persistent batched form: a grid sized to the resident blocks, each block
 // taking work items from a device counter (reset by a kernel launched just
 // before) until none is left. The same body as the flat form.
-template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
+template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT, bool PAIR>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
     ols_mixed4096_persistent_kernel(const SeriesDesc *__restrict__ desc, int nseries,
                                     long long total, unsigned long long *counter,
@@ -1004,17 +1077,18 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OC
     const long long local = item - d.item_begin;
     const int zg = (int)(local / d.nseg);
     const int sb = (int)(local % d.nseg);
-    const int z0 = d.row_off + zg * d.zpb;
-    const int z1 = min(d.row_off + d.nz, z0 + d.zpb);
+    const int per = unit_rows(d.zpb, PAIR);
+    const int z0 = d.row_off + zg * per;
+    const int z1 = min(d.row_off + unit_rows(d.nz, PAIR), z0 + per);
     const CandOut none{};
     // The thread index passes through an empty asm statement on every item, so
     // that nothing computed from it is hoisted out of this loop (held across
     // it, the addresses of one unit would not fit the register budget).
     int t;
     asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"((int)threadIdx.x));
-    mixed_unit<H, PF, NT, NW, SPLIT, false>(consts, static_cast<const c32 *>(d.spec), d.nbins,
-                                            bank, tw, d.power, d.ld, sb, true, U, half, z0, z1,
-                                            d.row_off, bank_log2, smem, s_max, none, t);
+    mixed_unit<H, PF, NT, NW, SPLIT, false, PAIR>(
+        consts, static_cast<const c32 *>(d.spec), d.nbins, bank, tw, d.power, d.ld, sb, true, U,
+        half, z0, z1, d.row_off, d.nz, bank_log2, smem, s_max, none, t);
   }
 }
 
@@ -1023,12 +1097,12 @@ static bool mixed_batch_persistent() {
   return !(e && *e == '0');  // the flat item grid with FDAS_BATCH_PERSISTENT=0
 }
 
-template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
-static hipError_t launch_mixed4096_batch(const BatchArgs &a, hipStream_t st) {
+template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT, bool PAIR>
+static hipError_t launch_mixed4096_batch_form(const BatchArgs &a, hipStream_t st) {
   if (mixed_batch_persistent()) {
     hipError_t e = launch_reset_counter(a.counter, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((ols_mixed4096_persistent_kernel<H, PF, NT, NW, OCC, SPLIT>),
+    hipLaunchKernelGGL((ols_mixed4096_persistent_kernel<H, PF, NT, NW, OCC, SPLIT, PAIR>),
                        dim3((unsigned)a.grid), dim3(64 * NW), 0, st, a.desc, a.nseries,
                        (long long)a.total, a.counter, static_cast<const H *>(a.bank),
                        static_cast<const c32 *>(a.tw), static_cast<const unsigned char *>(a.consts),
@@ -1036,19 +1110,30 @@ static hipError_t launch_mixed4096_batch(const BatchArgs &a, hipStream_t st) {
     return hipGetLastError();
   }
   if (a.total > (int64_t)0xffffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((ols_mixed4096_items_kernel<H, PF, NT, NW, OCC, SPLIT>), dim3((unsigned)a.total),
-                     dim3(64 * NW), 0, st, a.desc, a.nseries, static_cast<const H *>(a.bank),
-                     static_cast<const c32 *>(a.tw), static_cast<const unsigned char *>(a.consts),
-                     a.U, a.half, a.zpb, a.bank_log2);
+  hipLaunchKernelGGL((ols_mixed4096_items_kernel<H, PF, NT, NW, OCC, SPLIT, PAIR>),
+                     dim3((unsigned)a.total), dim3(64 * NW), 0, st, a.desc, a.nseries,
+                     static_cast<const H *>(a.bank), static_cast<const c32 *>(a.tw),
+                     static_cast<const unsigned char *>(a.consts), a.U, a.half, a.zpb, a.bank_log2);
   return hipGetLastError();
 }
 
+template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
+static hipError_t launch_mixed4096_batch(const BatchArgs &a, hipStream_t st) {
+  if constexpr (PF == 5) {
+    if (a.pair) return launch_mixed4096_batch_form<H, PF, NT, NW, OCC, SPLIT, true>(a, st);
+  }
+  return launch_mixed4096_batch_form<H, PF, NT, NW, OCC, SPLIT, false>(a, st);
+}
+
+// (the pair form has the occupancy of the single one: the same registers and LDS)
 template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
 static int mixed_batch_blocks_per_cu(int) {
   if (!mixed_batch_persistent()) return 1;  // flat launch: the grid is the item count
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, reinterpret_cast<const void *>(&ols_mixed4096_persistent_kernel<H, PF, NT, NW, OCC, SPLIT>),
+          &nb,
+          reinterpret_cast<const void *>(
+              &ols_mixed4096_persistent_kernel<H, PF, NT, NW, OCC, SPLIT, PF == 5>),
           64 * NW, 0) != hipSuccess)
     return 1;
   return nb;
@@ -1058,8 +1143,10 @@ template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
 static int mixed_grid_blocks_per_cu(int) {
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, reinterpret_cast<const void *>(&ols_mixed4096_kernel<H, PF, NT, NW, OCC, SPLIT, false>), 64 * NW,
-          0) != hipSuccess)
+          &nb,
+          reinterpret_cast<const void *>(
+              &ols_mixed4096_kernel<H, PF, NT, NW, OCC, SPLIT, false, PF == 5>),
+          64 * NW, 0) != hipSuccess)
     return 0;
   return nb;
 }
@@ -1074,6 +1161,7 @@ static OlsVariant make_mixed(const char *name, int precision) {
   v.nbuf = 1;
   v.precision = precision;
   v.split = SPLIT ? 1 : 0;
+  v.pair = PF == 5;
   // The forward FFT costs several templates' worth of time here; units of
   // up to 72 templates with a shorter last group measured fastest (17 to 101
   // swept on the paper-scale plane).
