@@ -536,8 +536,14 @@ int fdas_frontend_plan(fdas_frontend_t *out, int64_t n, int device, void *stream
     return set_error(FDAS_ERR_NOMEM, "front-end buffers: %s", hipGetErrorString(e));
   }
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  e = launch_twiddles(p->tw1, g.N1, s);
-  if (e == hipSuccess && g.N2 > 1) e = launch_twiddles(p->tw2, g.N2, s);
+  if (g.N2 == 1) {
+    e = launch_twiddles(p->tw1, g.N1, s);
+  } else {  // (the work buffer, M >= N1 entries, holds each plain table meanwhile)
+    e = launch_twiddles(p->work, g.N1, s);
+    if (e == hipSuccess) e = launch_stage_table(p->tw1, g.N1, M, p->work, s);
+    if (e == hipSuccess) e = launch_twiddles(p->work, g.N2, s);
+    if (e == hipSuccess) e = launch_stage_table(p->tw2, g.N2, M, p->work, s);
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) {
     free_frontend(p);

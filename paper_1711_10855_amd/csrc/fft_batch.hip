@@ -21,21 +21,6 @@
 
 namespace fdas {
 
-// LDS address, in the layout of the last stage, of frequency k.
-// After the last forward stage address a = sum_i d_i S_i holds frequency
-// k = d_0 + R_0 (d_1 + R_1 (d_2 + ...)), so the digits of k, least
-// significant first, are d_0, d_1, ...
-template <class Gm>
-__device__ __forceinline__ int addr_of_freq(int k) {
-  int a = 0;
-  static_for_up<0, Gm::P>([&](auto ic) {
-    constexpr int I = decltype(ic)::value;
-    a += (k % Gm::R[I]) * Gm::S(I);
-    k /= Gm::R[I];
-  });
-  return a;
-}
-
 template <class Gm, int G, int DIR>
 __global__ void __launch_bounds__(Gm::T *G)
     fft_batch_kernel(const c32 *__restrict__ in_, c32 *__restrict__ out_, int64_t batch,

@@ -101,6 +101,21 @@ __device__ __forceinline__ int stage_suffix(int t, int j) {
   return (t + j * Gm::T) % Gm::S(I);
 }
 
+// LDS address, in the layout of the last stage, of frequency k.
+// After the last forward stage address a = sum_i d_i S_i holds frequency
+// k = d_0 + R_0 (d_1 + R_1 (d_2 + ...)), so the digits of k, least
+// significant first, are d_0, d_1, ...
+template <class Gm>
+__device__ __forceinline__ int addr_of_freq(int k) {
+  int a = 0;
+  static_for_up<0, Gm::P>([&](auto ic) {
+    constexpr int I = decltype(ic)::value;
+    a += (k % Gm::R[I]) * Gm::S(I);
+    k /= Gm::R[I];
+  });
+  return a;
+}
+
 // Ordering of LDS traffic inside one wave (no workgroup barrier).
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
