@@ -61,7 +61,8 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
                                          const c32 *__restrict__ bank_, const c32 *__restrict__ tw_,
                                          float *__restrict__ power_, int64_t ld, int s, bool active,
                                          int U, int half, int z0, int z1, int row_base, int rows,
-                                         c32 *buf0, c32 *buf1, int t, const CandOut &cd) {
+                                         c32 *buf0, c32 *buf1, int t, const CandOut &cd,
+                                         CandLds *found = nullptr, int s_first = 0) {
   const auto spec = to_global(spec_);
   const auto bank = to_global(bank_);
   const auto tw = to_global(tw_);
@@ -162,8 +163,7 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
   auto emit = [&](int iz, const c32 (&y)[E]) {
     if constexpr (CAND) {
       // detection epilogue: one ballot on the lane's largest power skips a
-      // wave with no hit at all (the common case), else every lane takes part
-      // in each offer (one atomic per wave that has a hit)
+      // wave with no hit at all (the common case)
       constexpr int S0 = Gm::S(0), R0 = Gm::R[0];
       float pw[E], most = 0.f;
 #pragma unroll
@@ -172,13 +172,13 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
         most = e ? fmaxf(most, pw[e]) : pw[e];
       }
       if (__builtin_amdgcn_ballot_w64(active && most >= cd.thr) != 0ull) {
-#pragma nounroll
-        for (int e = 0; e < E; ++e) {
-          const int o = (e % R0) * S0 + t + (e / R0) * T;
-          const int64_t r = (int64_t)s * U + o - half;
-          const bool hit = active && o >= half && o < half + U && r < nbins && pw[e] >= cd.thr;
-          cand_offer(cd, hit, iz - row_base, r, pw[e]);
-        }
+        const int64_t left = nbins - (int64_t)s * U;
+        const int nkeep = active ? (int)(left < U ? left : U) : 0;
+        int o0 = t - half;  // (opaque: nothing made from it is held across the loop)
+        asm volatile("" : "+v"(o0));
+        cand_offer(
+            cd, found, iz - row_base, pw, [&](int e) { return o0 + (e % R0) * S0 + (e / R0) * T; },
+            nkeep, (s - s_first) * U, (int64_t)s_first * U);
       }
     } else if (kBufStore && active) {
       // Stores through a buffer resource that starts at plane column s U
@@ -365,22 +365,29 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
 }
 
 // Single spectrum: block -> (segment group, template group), template-group
-// major so concurrently running blocks share bank rows in L2.
+// major so concurrently running blocks share bank rows in L2 (see UnitGrid).
 template <class Gm, int G, bool TWREG, bool PF, int WPE, bool CAND, bool PAIR>
 __global__ void __launch_bounds__(Gm::T *G) __attribute__((amdgpu_waves_per_eu(WPE)))
     ols_fp32_kernel(const c32 *__restrict__ spec, int64_t nbins, const c32 *__restrict__ bank,
                     const c32 *__restrict__ tw, float *__restrict__ power, int64_t ld, int nseg,
-                    int U, int half, int nz, int zpb, int nsb, CandOut cand) {
+                    int U, int half, int nz, UnitGrid units, CandOut cand) {
   constexpr int T = Gm::T, NB = PAIR ? 2 : Gm::NBUF;
   __shared__ c32 lds[NB][G][Gm::LP];
   const int tid = threadIdx.x;
   const int sg = tid / T;
   const int t = tid % T;
-  const int sb = blockIdx.x % nsb;
-  const int zg = blockIdx.x / nsb;
+  int sb, z0, z1;
+  units.unit(blockIdx.x, &sb, &z0, &z1);
   const int s = sb * G + sg;
-  const int z0 = zg * zpb;
-  const int z1 = min(unit_rows(nz, PAIR), z0 + zpb);
+  if constexpr (CAND) {
+    __shared__ CandLds found;
+    if (tid == 0) cand_begin(&found);
+    __syncthreads();
+    ols_unit<Gm, TWREG, PF, CAND, PAIR>(spec, nbins, bank, tw, power, ld, s, s < nseg, U, half, z0,
+                                        z1, 0, nz, lds[0][sg], lds[NB - 1][sg], t, cand, &found, sb * G);
+    cand_end(cand, &found, (int64_t)sb * G * U);
+    return;
+  }
   ols_unit<Gm, TWREG, PF, CAND, PAIR>(spec, nbins, bank, tw, power, ld, s, s < nseg, U, half, z0,
                                       z1, 0, nz, lds[0][sg], lds[NB - 1][sg], t, cand);
 }
@@ -490,14 +497,11 @@ static bool batch_persistent() {
 
 template <class Gm, int G, bool TWREG, bool PF, int WPE, bool CAND, bool PAIR>
 static hipError_t launch_form(const OlsArgs &a, hipStream_t st) {
-  const int nsb = (a.nseg + G - 1) / G;
-  const int per = unit_rows(a.zpb, PAIR);
-  const int nzg = (unit_rows(a.nz, PAIR) + per - 1) / per;
-  const long blocks = (long)nsb * nzg;
-  hipLaunchKernelGGL((ols_fp32_kernel<Gm, G, TWREG, PF, WPE, CAND, PAIR>), dim3((unsigned)blocks),
+  const UnitGrid units = unit_grid(a, G, PAIR);
+  hipLaunchKernelGGL((ols_fp32_kernel<Gm, G, TWREG, PF, WPE, CAND, PAIR>), dim3((unsigned)units.blocks()),
                      dim3(Gm::T * G), 0, st, static_cast<const c32 *>(a.spec), a.nbins,
                      static_cast<const c32 *>(a.bank), static_cast<const c32 *>(a.tw), a.power,
-                     a.ld, a.nseg, a.U, a.half, a.nz, per, nsb, a.cand);
+                     a.ld, a.nseg, a.U, a.half, a.nz, units, a.cand);
   return hipGetLastError();
 }
 
@@ -579,6 +583,7 @@ static constexpr OlsVariant make_variant(const char *name) {
   v.nbuf = Gm::NBUF;
   v.precision = 0;
   v.pair = PWPE > 0;
+  v.unit_cost = 3.0f;
   v.lay.L = Gm::L;
   v.lay.T = Gm::T;
   v.lay.E = Gm::E;

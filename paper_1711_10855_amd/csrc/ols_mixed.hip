@@ -280,7 +280,7 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
                                            bool active, int U, int half, int z0, int z1,
                                            int row_base, int rows, int bank_log2,
                                            unsigned char *smem, float *s_max, const CandOut &cd,
-                                           int t_in = -1) {
+                                           int t_in = -1, CandLds *found = nullptr) {
   typedef typename Vec<H>::v8 v8;
   constexpr int L = 4096;
   constexpr int TPW = 16 / NW;
@@ -576,7 +576,7 @@ __device__ __forceinline__ void mixed_unit(const unsigned char *__restrict__ con
       if constexpr (CAND) {  // detection epilogue instead of the plane (all lanes offer)
         const bool any = v[0] >= cd.thr || v[1] >= cd.thr || v[2] >= cd.thr || v[3] >= cd.thr;
         if (__builtin_amdgcn_ballot_w64(active && any) == 0ull) continue;  // no hit in the wave
-        offer4(cd, v, active, o0, half, U, r0, nbins, izr - row_base);
+        offer4(cd, found, v, o0 - half, active ? nkeep : 0, (int64_t)s * U, izr - row_base);
         continue;
       }
       const auto dst = prow + r0;
@@ -979,13 +979,20 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OC
     ols_mixed4096_kernel(const c32 *__restrict__ spec, int64_t nbins, const H *__restrict__ bank,
                          const c32 *__restrict__ tw, const unsigned char *__restrict__ consts,
                          float *__restrict__ power, int64_t ld, int nseg, int U, int half, int nz,
-                         int zpb, int nsb, int bank_log2, CandOut cand) {
+                         UnitGrid units, int bank_log2, CandOut cand) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[mix_smem<SPLIT, PF>()];
   __shared__ float s_max[NW];
-  const int sb = blockIdx.x % nsb;
-  const int zg = blockIdx.x / nsb;
-  const int z0 = zg * zpb;
-  const int z1 = min(unit_rows(nz, PAIR), z0 + zpb);
+  int sb, z0, z1;
+  units.unit(blockIdx.x, &sb, &z0, &z1);
+  if constexpr (CAND) {  // (the forward transform's barriers come before the first offer)
+    __shared__ CandLds found;
+    if (threadIdx.x == 0) cand_begin(&found);
+    mixed_unit<H, PF, NT, NW, SPLIT, CAND, PAIR>(consts, spec, nbins, bank, tw, power, ld, sb,
+                                                 sb < nseg, U, half, z0, z1, 0, nz, bank_log2,
+                                                 smem, s_max, cand, -1, &found);
+    cand_end(cand, &found, (int64_t)sb * U);
+    return;
+  }
   mixed_unit<H, PF, NT, NW, SPLIT, CAND, PAIR>(consts, spec, nbins, bank, tw, power, ld, sb,
                                                sb < nseg, U, half, z0, z1, 0, nz, bank_log2, smem,
                                                s_max, cand);
@@ -1026,15 +1033,12 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OC
 
 template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT, bool CAND, bool PAIR>
 static hipError_t launch_mixed4096_form(const OlsArgs &a, hipStream_t st) {
-  const int nsb = a.nseg;
-  const int per = unit_rows(a.zpb, PAIR);
-  const int nzg = (unit_rows(a.nz, PAIR) + per - 1) / per;
-  const long blocks = (long)nsb * nzg;
+  const UnitGrid units = unit_grid(a, 1, PAIR);
   hipLaunchKernelGGL((ols_mixed4096_kernel<H, PF, NT, NW, OCC, SPLIT, CAND, PAIR>),
-                     dim3((unsigned)blocks), dim3(64 * NW), 0, st,
+                     dim3((unsigned)units.blocks()), dim3(64 * NW), 0, st,
                      static_cast<const c32 *>(a.spec), a.nbins, static_cast<const H *>(a.bank),
                      static_cast<const c32 *>(a.tw), static_cast<const unsigned char *>(a.consts),
-                     a.power, a.ld, a.nseg, a.U, a.half, a.nz, per, nsb, a.bank_log2, a.cand);
+                     a.power, a.ld, a.nseg, a.U, a.half, a.nz, units, a.bank_log2, a.cand);
   return hipGetLastError();
 }
 
@@ -1166,6 +1170,7 @@ static OlsVariant make_mixed(const char *name, int precision) {
   // up to 72 templates with a shorter last group measured fastest (17 to 101
   // swept on the paper-scale plane).
   v.zpb_target = 72;
+  v.unit_cost = SPLIT ? 5.0f : 8.0f;
   v.lay.L = 4096;
   v.lay.T = 256;
   v.lay.E = 16;

@@ -159,7 +159,8 @@ __device__ __forceinline__ void unit2048(const unsigned char *__restrict__ const
                                          float *__restrict__ power_, int64_t ld, int s,
                                          bool active, int U, int half, int z0, int z1,
                                          int row_base, int bank_log2, unsigned char *smem,
-                                         float *s_max, const CandOut &cd, int t_in = -1) {
+                                         float *s_max, const CandOut &cd, int t_in = -1,
+                                         CandLds *found = nullptr) {
   typedef typename V<H>::v8 v8;
   typedef typename V<H>::v4 v4;
   const auto consts = to_global(reinterpret_cast<const v8 *>(consts_));
@@ -351,7 +352,7 @@ __device__ __forceinline__ void unit2048(const unsigned char *__restrict__ const
     if constexpr (CAND) {
       const bool any = v[0] >= cd.thr || v[1] >= cd.thr || v[2] >= cd.thr || v[3] >= cd.thr;
       if (__builtin_amdgcn_ballot_w64(active && any) == 0ull) return;
-      offer4(cd, v, active, o0, half, U, r0, nbins, izr - row_base);
+      offer4(cd, found, v, o0 - half, active ? nkeep : 0, (int64_t)s * U, izr - row_base);
       return;
     }
     const auto dst = prow + r0;
@@ -450,13 +451,19 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OC
     ols_mixed2048_kernel(const c32 *__restrict__ spec, int64_t nbins, const H *__restrict__ bank,
                          const c32 *__restrict__ tw, const unsigned char *__restrict__ consts,
                          float *__restrict__ power, int64_t ld, int nseg, int U, int half, int nz,
-                         int zpb, int nsb, int bank_log2, CandOut cand) {
+                         UnitGrid units, int bank_log2, CandOut cand) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kSmem];
   __shared__ float s_max[NW];
-  const int sb = blockIdx.x % nsb;
-  const int zg = blockIdx.x / nsb;
-  const int z0 = zg * zpb;
-  const int z1 = min(nz, z0 + zpb);
+  int sb, z0, z1;
+  units.unit(blockIdx.x, &sb, &z0, &z1);
+  if constexpr (CAND) {  // (the forward transform's barriers come before the first offer)
+    __shared__ CandLds found;
+    if (threadIdx.x == 0) cand_begin(&found);
+    unit2048<H, NT, CAND>(consts, spec, nbins, bank, tw, power, ld, sb, sb < nseg, U, half, z0, z1,
+                          0, bank_log2, smem, s_max, cand, -1, &found);
+    cand_end(cand, &found, (int64_t)sb * U);
+    return;
+  }
   unit2048<H, NT, CAND>(consts, spec, nbins, bank, tw, power, ld, sb, sb < nseg, U, half, z0, z1,
                         0, bank_log2, smem, s_max, cand);
 }
@@ -536,21 +543,20 @@ static bool batch_persistent() {
 
 template <class H, bool NT, int OCC>
 static hipError_t launch_single(const OlsArgs &a, hipStream_t st) {
-  const int nsb = a.nseg;
-  const int nzg = (a.nz + a.zpb - 1) / a.zpb;
-  const long blocks = (long)nsb * nzg;
+  const UnitGrid units = unit_grid(a, 1, false);
+  const long blocks = units.blocks();
   if (a.cand.count)
     hipLaunchKernelGGL((ols_mixed2048_kernel<H, NT, OCC, true>), dim3((unsigned)blocks),
                        dim3(64 * NW), 0, st, static_cast<const c32 *>(a.spec), a.nbins,
                        static_cast<const H *>(a.bank), static_cast<const c32 *>(a.tw),
                        static_cast<const unsigned char *>(a.consts), a.power, a.ld, a.nseg, a.U,
-                       a.half, a.nz, a.zpb, nsb, a.bank_log2, a.cand);
+                       a.half, a.nz, units, a.bank_log2, a.cand);
   else
     hipLaunchKernelGGL((ols_mixed2048_kernel<H, NT, OCC, false>), dim3((unsigned)blocks),
                        dim3(64 * NW), 0, st, static_cast<const c32 *>(a.spec), a.nbins,
                        static_cast<const H *>(a.bank), static_cast<const c32 *>(a.tw),
                        static_cast<const unsigned char *>(a.consts), a.power, a.ld, a.nseg, a.U,
-                       a.half, a.nz, a.zpb, nsb, a.bank_log2, a.cand);
+                       a.half, a.nz, units, a.bank_log2, a.cand);
   return hipGetLastError();
 }
 
@@ -605,6 +611,7 @@ static OlsVariant make(const char *name, int precision) {
   v.precision = precision;
   v.split = 0;
   v.zpb_target = 72;
+  v.unit_cost = 8.0f;
   v.lay.L = L;
   v.lay.T = 128;
   v.lay.E = 16;

@@ -26,29 +26,94 @@ struct CandOut {
   float thr;
 };
 
-// Called by every lane of the wave together (not under divergent control
-// flow); lanes with `hit` set append (row, r, p). One atomic per wave that has
-// any hit: lanes take consecutive slots in lane order.
-__device__ __forceinline__ void cand_offer(const CandOut &cd, bool hit, int row, int64_t r,
-                                           float p) {
+// Detection kernels collect a block's candidates in LDS and list them when the
+// unit ends: a hit then costs an LDS atomic, not a round trip to memory. A
+// segment with a strong signal has hits in most rows, so its block is the one
+// that the launch waits for (2^21 bins x 101 rows in FP32 with eight signals,
+// against 223 us without a hit: 276 us with a global atomic per power, 254 with
+// one per template and wave, 228 collected).
+constexpr int kCandLds = 320;
+struct CandLds {
+  int n;    // entries asked for; from `lim` on they did not fit
+  int lim;
+  unsigned long long base;
+  struct {
+    int row;
+    float power;
+    int rel;  // bin - the block's first kept bin
+  } e[kCandLds];
+};
+__device__ __forceinline__ void cand_store(gptr<Cand> to, int row, float p, int64_t r) {
   typedef int i4v __attribute__((ext_vector_type(4)));
-  const unsigned long long mask = __builtin_amdgcn_ballot_w64(hit);
-  if (mask == 0ull) return;
-  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  const int first = __builtin_ctzll(mask);
-  unsigned long long base = 0ull;
-  if (lane == first) base = atomicAdd(cd.count, (unsigned long long)__builtin_popcountll(mask));
-  const unsigned lo = __builtin_amdgcn_readlane((unsigned)base, first);
-  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(base >> 32), first);
-  base = ((unsigned long long)hi << 32) | lo;
-  if (hit) {
-    const unsigned long long i =
-        base + (unsigned long long)__builtin_popcountll(mask & ((1ull << lane) - 1ull));
-    if (i < (unsigned long long)cd.cap) {
-      const i4v v = {row, __builtin_bit_cast(int, p), (int)(uint64_t)r, (int)((uint64_t)r >> 32)};
-      *(gptr<i4v>)(cd.list + i) = v;  // one 16-byte store
-    }
+  const i4v v = {row, __builtin_bit_cast(int, p), (int)(uint64_t)r, (int)((uint64_t)r >> 32)};
+  *(gptr<i4v>)to = v;  // one 16-byte store
+}
+
+// By one thread, before a barrier that precedes the first offer.
+__device__ __forceinline__ void cand_begin(CandLds *b) {
+  b->n = 0;
+  b->lim = kCandLds;
+}
+
+// Called by every lane of the wave together (not under divergent control
+// flow): lists, at plane row `row`, the lane's powers p[e] that reach the
+// threshold at a kept output, at(e) in [0, nkeep). Output 0 is bin rel0 of the
+// block's, whose first is bin r0 of the plane.
+template <int N, class At>
+__device__ __forceinline__ void cand_offer(const CandOut &cd, CandLds *b, int row,
+                                           const float (&p)[N], At at, int nkeep, int rel0,
+                                           int64_t r0) {
+  unsigned long long hit[N];
+  int total = 0;
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    hit[e] = __builtin_amdgcn_ballot_w64(p[e] >= cd.thr && (unsigned)at(e) < (unsigned)nkeep);
+    total += __builtin_popcountll(hit[e]);
   }
+  if (total == 0) return;
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  int pos = 0;
+  if (lane == 0) pos = atomicAdd(&b->n, total);
+  pos = __builtin_amdgcn_readfirstlane(pos);
+  const bool fits = pos + total <= kCandLds;
+  unsigned long long base = 0ull;
+  if (!fits) {  // straight to the list
+    if (lane == 0) {
+      atomicMin(&b->lim, pos);
+      base = atomicAdd(cd.count, (unsigned long long)total);
+    }
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)base);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(base >> 32));
+    base = ((unsigned long long)hi << 32) | lo;
+    pos = 0;
+  }
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    if (hit[e] == 0ull) continue;
+    if (hit[e] >> lane & 1ull) {
+      const int k = pos + (int)__builtin_amdgcn_mbcnt_hi(
+                              (unsigned)(hit[e] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hit[e], 0u));
+      const int rel = rel0 + at(e);
+      if (fits)
+        b->e[k] = {row, p[e], rel};
+      else if (base + (unsigned)k < (unsigned long long)cd.cap)
+        cand_store((gptr<Cand>)cd.list + base + k, row, p[e], r0 + rel);
+    }
+    pos += __builtin_popcountll(hit[e]);
+  }
+}
+
+// By the whole block after its last offer (block-wide barriers inside); r0 as
+// in the offers.
+__device__ __forceinline__ void cand_end(const CandOut &cd, CandLds *b, int64_t r0) {
+  __syncthreads();
+  const int m = b->n < b->lim ? b->n : b->lim;
+  if (m == 0) return;
+  if (threadIdx.x == 0) b->base = atomicAdd(cd.count, (unsigned long long)m);
+  __syncthreads();
+  for (int i = threadIdx.x; i < m; i += blockDim.x)
+    if (b->base + (unsigned)i < (unsigned long long)cd.cap)
+      cand_store((gptr<Cand>)cd.list + b->base + i, b->e[i].row, b->e[i].power, r0 + b->e[i].rel);
 }
 
 struct OlsArgs {
@@ -62,7 +127,8 @@ struct OlsArgs {
   int U;             // L - m
   int half;          // m / 2
   int nz;            // rows to produce
-  int zpb;           // templates per work unit
+  int n1, zpb1, zpb2;  // templates per work unit: zpb1 on the first n1 segment
+                       // groups, zpb2 on the others
   int bank_log2;     // mixed precision: the bank is stored times 2^bank_log2
   const void *consts;  // mixed precision: per-lane constants table
   CandOut cand;        // detection epilogue (count == nullptr: store the plane)
@@ -74,6 +140,30 @@ struct OlsArgs {
 // of rows the middle one stands alone).
 __host__ __device__ inline int unit_rows(int rows, bool pair) {
   return pair ? (rows + 1) >> 1 : rows;
+}
+
+// The work units of a single-spectrum launch, one per block: first those of
+// the segment groups [0, n1), of per1 rows (or pairs) each, then those of the
+// others, of per2; row-group major inside each part.
+struct UnitGrid {
+  int nsb, rows, n1, per1, per2;
+  __host__ long blocks() const {
+    return (long)n1 * ((rows + per1 - 1) / per1) + (long)(nsb - n1) * ((rows + per2 - 1) / per2);
+  }
+  __device__ __forceinline__ void unit(unsigned b, int *sb, int *z0, int *z1) const {
+    const unsigned b1 = (unsigned)n1 * (unsigned)((rows + per1 - 1) / per1);
+    const bool second = b >= b1;
+    const unsigned i = second ? b - b1 : b, n = second ? nsb - n1 : n1;
+    const int per = second ? per2 : per1;
+    *sb = (second ? n1 : 0) + (int)(i % n);
+    *z0 = (int)(i / n) * per;
+    *z1 = *z0 + per < rows ? *z0 + per : rows;
+  }
+};
+// (G: segments per group)
+inline UnitGrid unit_grid(const OlsArgs &a, int G, bool pair) {
+  return {(a.nseg + G - 1) / G, unit_rows(a.nz, pair), a.n1, unit_rows(a.zpb1, pair),
+          unit_rows(a.zpb2, pair)};
 }
 
 // One series of a batch as the persistent kernel sees it.
@@ -109,8 +199,9 @@ struct OlsVariant {
   int precision;     // FDAS_FP32 (0), FDAS_MIXED_FP16 (1), FDAS_MIXED_BF16 (2)
   int split;         // 1: hi + lo split products (FDAS_FLAG_SPLIT)
   int pair;          // 1: has a pair form, used where the bank's rows mirror
-  int zpb_target;    // > 0: templates per work unit fixed near this (balanced
-                     // groups); 0: chosen per launch from the grid's rounds
+  int zpb_target;    // > 0: templates per work item of a batch that does not fill
+                     // the GPU many times over; 0: near-equal groups of at most 40
+  float unit_cost;   // what a unit's forward transform takes, in templates
   LayoutDesc lay;
   int lds_bytes;
   hipError_t (*launch)(const OlsArgs &, hipStream_t);

@@ -476,38 +476,56 @@ int plan_bank_natural(fdas_plan_t pl, void *dst, hipStream_t s) {
   return FDAS_OK;
 }
 
-// Templates per work unit for a grid of nsb segment groups: the grid runs in
-// ceil(blocks / slots) rounds, each as long as one unit (zpb inverse FFTs plus
-// about one forward FFT); pick the group count that minimises that product.
-static int launch_zpb(fdas_plan_t pl, int64_t nsb) {
-  if (pl->zpb_forced || pl->var->zpb_target > 0) return pl->zpb;
+// Blocks of the plan's kernel that the GPU holds at once (0 if unknown).
+static int plan_slots(fdas_plan_t pl) {
   if (!pl->slots) {
     int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device) != hipSuccess)
-      return pl->zpb;
     const int per = pl->var->grid_blocks_per_cu ? pl->var->grid_blocks_per_cu(pl->pair) : 0;
-    if (per <= 0 || cus <= 0) return pl->zpb;
-    pl->slots = cus * per;
+    if (per > 0 &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device) == hipSuccess)
+      pl->slots = cus * per;
   }
-  double best = 0.0;
-  int best_zpb = pl->zpb;
-  const int n = unit_rows(pl->nz, pl->pair), each = pl->pair ? 2 : 1;
-  for (int ng = 1; ng <= std::min(n, 16); ++ng) {
-    const int per = (n + ng - 1) / ng;
-    const int groups = (n + per - 1) / per;
-    const double rounds = std::ceil((double)(nsb * groups) / (double)pl->slots);
-    const double cost = rounds * (each * per + 1.0);
-    if (ng == 1 || cost < best * 0.999) {
-      best = cost;
-      best_zpb = std::min(each * per, pl->nz);
+  return pl->slots;
+}
+
+// Templates per work unit of a launch over nsb segment groups. The blocks run
+// in rounds of `slots`, a round as long as its longest unit (its templates
+// and unit_cost for the forward transform). Segment groups that fill whole
+// rounds take all rows in one unit, which pays the forward transform once;
+// those that are left over are split finely enough to fill one more round or
+// a few short ones. (2^20 bins x 101 rows in split BF16: 274 segments on 256
+// slots. As units of 72 and 29 rows, short ones last, 18 long units started
+// when the rest had done theirs: 195 us, against 173 with 256 whole units and
+// the other 18 segments in units of 8. 2^21 x 101 in FP32: 294 against 276 us.
+// 65536 bins in FP16, 18 segments on 512 slots: 61 against 16 us.)
+struct UnitSplit {
+  int64_t n1;
+  int zpb1, zpb2;
+};
+static UnitSplit launch_split(fdas_plan_t pl, int64_t nsb) {
+  const int slots = pl->zpb_forced ? 0 : plan_slots(pl);
+  if (slots <= 0) return {0, pl->zpb, pl->zpb};
+  const int each = pl->pair ? 2 : 1, n = unit_rows(pl->nz, pl->pair);
+  const double fwd = pl->var->unit_cost;
+  UnitSplit best{0, pl->nz, pl->nz};
+  double best_cost = 0.0;
+  const int64_t full = nsb / slots;
+  for (int64_t k = full; k >= 0 && k >= full - 1; --k) {
+    const int64_t rest = nsb - k * slots;
+    for (int g = 1; g <= n; ++g) {
+      const int per = (n + g - 1) / g;
+      if (g > 1 && per == (n + g - 2) / (g - 1)) continue;  // the same units as before
+      const int64_t rounds = (rest * ((n + per - 1) / per) + slots - 1) / slots;
+      const double cost =
+          (double)k * (each * n + fwd) + (double)rounds * ((double)each * per + fwd);
+      if (best_cost == 0.0 || cost < best_cost * 0.999) {
+        best_cost = cost;
+        best = {k * slots, pl->nz, std::min(each * per, pl->nz)};
+      }
+      if (rest == 0) break;
     }
   }
-  // On grids of two or more full rounds, units of 40 templates with the
-  // remainder last beat equal groups (the short units fill the end of the
-  // launch; 2-3% on the 2^21-bin plane at 65 and 101 rows).
-  const int tz = default_zpb(pl->nz, kFp32UnitTarget);
-  if (nsb * ((pl->nz + tz - 1) / tz) >= 2 * (int64_t)pl->slots) best_zpb = tz;
-  return best_zpb;
+  return best;
 }
 
 static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *power, int64_t ld,
@@ -515,9 +533,9 @@ static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *p
   const int64_t nseg = (nbins + pl->U - 1) / pl->U;
   if (nseg > INT_MAX / 2) return set_error(FDAS_ERR_UNSUPPORTED, "nbins %lld too large", (long long)nbins);
   const int64_t nsb = (nseg + pl->var->G - 1) / pl->var->G;
-  const int zpb = launch_zpb(pl, nsb);
-  pl->last_zpb = zpb;
-  const int64_t nzg = (pl->nz + zpb - 1) / zpb;
+  const UnitSplit split = launch_split(pl, nsb);
+  pl->last_zpb = split.n1 ? split.zpb1 : split.zpb2;
+  const int64_t nzg = (pl->nz + split.zpb2 - 1) / split.zpb2;
   if (nsb * nzg > (int64_t)UINT_MAX)
     return set_error(FDAS_ERR_UNSUPPORTED, "grid of %lld blocks too large", (long long)(nsb * nzg));
   OlsArgs a;
@@ -531,7 +549,9 @@ static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *p
   a.U = pl->U;
   a.half = pl->m / 2;
   a.nz = pl->nz;
-  a.zpb = zpb;
+  a.n1 = (int)split.n1;
+  a.zpb1 = split.zpb1;
+  a.zpb2 = split.zpb2;
   a.bank_log2 = 0;
   while ((1 << a.bank_log2) < pl->L) ++a.bank_log2;
   a.consts = pl->consts;
@@ -599,15 +619,9 @@ static int series_desc(fdas_plan_t pl, const fdas_series &x, int i, int zpb, Ser
 // plan's unit size, as does a size fixed by FDAS_ZPB or the autotuner.
 static int batch_zpb(fdas_plan_t pl, int64_t nsb) {
   if (pl->zpb_forced) return pl->zpb;
-  if (!pl->slots) {
-    int cus = 0;
-    const int per = pl->var->grid_blocks_per_cu ? pl->var->grid_blocks_per_cu(pl->pair) : 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device) != hipSuccess ||
-        per <= 0 || cus <= 0)
-      return pl->zpb;
-    pl->slots = cus * per;
-  }
-  return nsb >= 8 * (int64_t)pl->slots ? INT_MAX / 2 : pl->zpb;
+  const int slots = plan_slots(pl);
+  if (slots <= 0) return pl->zpb;
+  return nsb >= 8 * (int64_t)slots ? INT_MAX / 2 : pl->zpb;
 }
 
 static int64_t series_items(const SeriesDesc &d, int G, int pair) {
