@@ -203,7 +203,12 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(__builtin_fmaf(v.x, v.x, v.y * v.y)),
                                                 rs, soff[j * R0 + n], 0, 2 /* nontemporal */);
         }
-    } else if (active) {  // segments narrower than a wave: per-lane addresses
+    } else if (active) {
+      // Segments narrower than a wave: per-lane addresses, in pieces of 4 T
+      // bytes. Where rows are not 128-byte aligned the pieces end inside
+      // lines, which the L2 has to put together before they leave it: these
+      // stores are not nontemporal (2097151 bins x 51 rows at 256 points: 145
+      // against 251 us; aligned rows are no slower).
       constexpr int S0 = Gm::S(0), R0 = Gm::R[0];
       const auto prow = power + (int64_t)(iz - row_base) * ld;
 #pragma unroll
@@ -214,7 +219,7 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
           const int64_t r = (int64_t)s * U + o - half;
           if (o >= half && o < half + U && r < nbins) {
             const c32 v = y[j * R0 + n];
-            __builtin_nontemporal_store(__builtin_fmaf(v.x, v.x, v.y * v.y), prow + r);
+            prow[r] = __builtin_fmaf(v.x, v.x, v.y * v.y);
           }
         }
     }
