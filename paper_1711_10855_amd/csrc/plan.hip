@@ -476,14 +476,19 @@ int plan_bank_natural(fdas_plan_t pl, void *dst, hipStream_t s) {
   return FDAS_OK;
 }
 
+// Compute units of the plan's GPU (0 if unknown).
+static int plan_cus(fdas_plan_t pl) {
+  if (!pl->cus && hipDeviceGetAttribute(&pl->cus, hipDeviceAttributeMultiprocessorCount,
+                                        pl->device) != hipSuccess)
+    pl->cus = 0;
+  return pl->cus;
+}
+
 // Blocks of the plan's kernel that the GPU holds at once (0 if unknown).
 static int plan_slots(fdas_plan_t pl) {
   if (!pl->slots) {
-    int cus = 0;
     const int per = pl->var->grid_blocks_per_cu ? pl->var->grid_blocks_per_cu(pl->pair) : 0;
-    if (per > 0 &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device) == hipSuccess)
-      pl->slots = cus * per;
+    if (per > 0) pl->slots = plan_cus(pl) * per;
   }
   return pl->slots;
 }
@@ -583,9 +588,8 @@ int plan_convolve_candidates(fdas_plan_t pl, const void *spec, int64_t nbins, fl
 }
 
 // One series of a batch: check its zmax against the plan's z grid and fill
-// its descriptor (all but the first work item); `cost` orders the series.
-static int series_desc(fdas_plan_t pl, const fdas_series &x, int i, int zpb, SeriesDesc *d,
-                       double *cost) {
+// its descriptor (all but its work items); `cost` orders the series.
+static int series_desc(fdas_plan_t pl, const fdas_series &x, int i, SeriesDesc *d, double *cost) {
   const double dz = pl->p.dz;
   if (!std::isfinite(x.zmax) || x.zmax < 0.0 || x.zmax > pl->p.zmax * (1.0 + 1e-12) + 1e-12)
     return set_error(FDAS_ERR_INVALID, "series %d: zmax %g outside [0, %g]", i, x.zmax, pl->p.zmax);
@@ -604,24 +608,64 @@ static int series_desc(fdas_plan_t pl, const fdas_series &x, int i, int zpb, Ser
   d->nseg = (int)nseg;
   d->nz = per * ((int)std::nearbyint(span) + 1);
   d->row_off = per * (int)std::nearbyint(off);
-  // near-equal template groups of at most zpb templates
-  const int ng = (d->nz + zpb - 1) / zpb;
-  d->zpb = (d->nz + ng - 1) / ng;
+  d->zpb = d->nz;
   *cost = (double)d->nz * (double)x.nbins;
   return FDAS_OK;
 }
 
-// Templates per work item of a batch whose series have `nsb` segment groups
-// in all. A batch that fills the grid many times over has no tail to
-// balance, and one unit per (series, segment) pays the forward transform
-// once per segment: 3-4% faster than units of 40 (FP32) or 72 (matrix cores)
-// on 118 series of 2^21 bins at 201 templates. Smaller batches keep the
-// plan's unit size, as does a size fixed by FDAS_ZPB or the autotuner.
-static int batch_zpb(fdas_plan_t pl, int64_t nsb) {
-  if (pl->zpb_forced) return pl->zpb;
-  const int slots = plan_slots(pl);
-  if (slots <= 0) return pl->zpb;
-  return nsb >= 8 * (int64_t)slots ? INT_MAX / 2 : pl->zpb;
+// Work items of a batch, its series in the order in which blocks take them
+// (largest first): one item per (series, segment) with all rows, which pays the
+// forward transform once, but for the series from `tail` on, which make up the
+// last round of the GPU's block slots: those in near-equal groups of at most
+// `zpb` templates, so that the blocks end together. The size is the one whose
+// work, spread over the slots, and half an item for the uneven end are least;
+// a batch of less than a round is all tail. (12 series of 2^19 .. 2^21 bins and
+// 33 .. 101 rows in FP32: 1302 us in groups of at most 40 rows, 1257 this way; 6
+// series of 95000 .. 190000 bins in FP16: 116 against 86 us.) FDAS_ZPB or the
+// autotuner fixes one size for all. get(k): segment groups and rows of the
+// series at place k.
+struct BatchUnits {
+  int tail, zpb;
+};
+template <class Get>
+static BatchUnits batch_units(fdas_plan_t pl, int n, Get &&get) {
+  if (pl->zpb_forced || plan_cus(pl) <= 0) return {0, pl->zpb};
+  const double slots = (double)pl->cus * std::max(1, pl->var->batch_blocks_per_cu(pl->pair));
+  const double fwd = pl->var->unit_cost;
+  int rows = 0;
+  for (int k = 0; k < n; ++k) rows = std::max(rows, get(k).second);
+  int tail = n, tail_rows = 1;
+  double work = 0.0;
+  while (tail > 0 && work < slots * (rows + fwd)) {
+    const auto x = get(--tail);
+    work += (double)x.first * (x.second + fwd);
+    tail_rows = std::max(tail_rows, x.second);
+  }
+  double head = 0.0;
+  for (int k = 0; k < tail; ++k) head += (double)get(k).first * (get(k).second + fwd);
+  BatchUnits best{tail, tail_rows};
+  double best_time = 0.0;
+  for (int groups : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+    int zpb = (tail_rows + groups - 1) / groups;
+    if (pl->pair) zpb += zpb & 1;
+    work = head;
+    for (int k = tail; k < n; ++k) {
+      const auto x = get(k);
+      work += (double)x.first * (x.second + fwd * ((x.second + zpb - 1) / zpb));
+    }
+    const double item = zpb + fwd, time = std::max(item, work / slots + 0.5 * item);
+    if (best_time == 0.0 || time < best_time * 0.999) {
+      best_time = time;
+      best.zpb = zpb;
+    }
+  }
+  return best;
+}
+
+// Sets a series' templates per item: near-equal groups of at most zpb.
+static void set_units(SeriesDesc *d, int zpb) {
+  const int ng = (d->nz + zpb - 1) / zpb;
+  d->zpb = (d->nz + ng - 1) / ng;
 }
 
 static int64_t series_items(const SeriesDesc &d, int G, int pair) {
@@ -634,11 +678,7 @@ static int64_t series_items(const SeriesDesc &d, int G, int pair) {
 // Launch arguments of the batch kernel over a descriptor table on the device.
 static int batch_args(fdas_plan_t pl, const SeriesDesc *d_desc, int nseries, int64_t total,
                       unsigned long long *counter, BatchArgs *a) {
-  if (!pl->cus) {
-    const hipError_t e =
-        hipDeviceGetAttribute(&pl->cus, hipDeviceAttributeMultiprocessorCount, pl->device);
-    if (e != hipSuccess) return hip_error(e, "CU count");
-  }
+  if (plan_cus(pl) <= 0) return set_error(FDAS_ERR_DEVICE, "CU count unknown");
   const int per_cu = std::max(1, pl->var->batch_blocks_per_cu(pl->pair));
   a->desc = d_desc;
   a->nseries = nseries;
@@ -688,30 +728,27 @@ int plan_convolve_batch(fdas_plan_t pl, const fdas_series *series, int nseries, 
   const int G = pl->var->G;
   std::vector<SeriesDesc> desc(nseries);
   std::vector<double> cost(nseries);
-  int64_t nsb = 0;
   for (int i = 0; i < nseries; ++i) {
-    const int st = series_desc(pl, series[i], i, pl->zpb, &desc[i], &cost[i]);
+    const int st = series_desc(pl, series[i], i, &desc[i], &cost[i]);
     if (st != FDAS_OK) return st;
-    nsb += (desc[i].nseg + G - 1) / G;
   }
-  const int zpb = batch_zpb(pl, nsb);
-  int most = 0;  // templates per unit of the largest unit, for plan info
-  for (int i = 0; i < nseries; ++i) {
-    const int ng = (desc[i].nz + zpb - 1) / zpb;
-    desc[i].zpb = (desc[i].nz + ng - 1) / ng;
-    most = std::max(most, desc[i].zpb);
-  }
-  pl->last_zpb = most;
   std::vector<int> order(nseries);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
   std::vector<SeriesDesc> sorted(nseries);
+  for (int k = 0; k < nseries; ++k) sorted[k] = desc[order[k]];
+  const BatchUnits units = batch_units(pl, nseries, [&](int k) {
+    return std::make_pair((int64_t)(sorted[k].nseg + G - 1) / G, sorted[k].nz);
+  });
   int64_t total = 0;
+  int most = 0;  // templates per unit of the largest unit, for plan info
   for (int k = 0; k < nseries; ++k) {
-    sorted[k] = desc[order[k]];
+    if (k >= units.tail) set_units(&sorted[k], units.zpb);
+    most = std::max(most, sorted[k].zpb);
     sorted[k].item_begin = total;
     total += series_items(sorted[k], G, pl->pair);
   }
+  pl->last_zpb = most;
   if (total == 0) return FDAS_OK;
 
   hipError_t e = hipSuccess;
@@ -809,18 +846,21 @@ int plan_convolve_batch_noalloc(fdas_plan_t pl, const fdas_series *series, int n
   const int G = pl->var->G;
   double cost[kNoAllocMaxSeries];
   int order[kNoAllocMaxSeries];
-  int64_t nsb = 0;
   for (int i = 0; i < nseries; ++i) {
     SeriesDesc d;
-    const int st = series_desc(pl, series[i], i, pl->zpb, &d, &cost[i]);
+    const int st = series_desc(pl, series[i], i, &d, &cost[i]);
     if (st != FDAS_OK) return st;
     order[i] = i;
-    nsb += (d.nseg + G - 1) / G;
   }
-  const int zpb = batch_zpb(pl, nsb);
   // largest first, ties in input order (the order the graph path uses)
   std::sort(order, order + nseries,
             [&](int a, int b) { return cost[a] > cost[b] || (cost[a] == cost[b] && a < b); });
+  const BatchUnits units = batch_units(pl, nseries, [&](int k) {
+    SeriesDesc d;
+    double c = 0.0;
+    (void)series_desc(pl, series[order[k]], order[k], &d, &c);
+    return std::make_pair((int64_t)(d.nseg + G - 1) / G, d.nz);
+  });
   void *base = nullptr;
   int st = noalloc_scratch(pl->device, &base);
   if (st != FDAS_OK) return st;
@@ -834,7 +874,8 @@ int plan_convolve_batch_noalloc(fdas_plan_t pl, const fdas_series *series, int n
   for (int k = 0; k < nseries; ++k) {
     SeriesDesc &d = chunk.d[chunk.n];
     double c = 0.0;
-    (void)series_desc(pl, series[order[k]], order[k], zpb, &d, &c);
+    (void)series_desc(pl, series[order[k]], order[k], &d, &c);
+    if (k >= units.tail) set_units(&d, units.zpb);
     d.item_begin = total;
     total += series_items(d, G, pl->pair);
     if (++chunk.n == kDescChunk || k == nseries - 1) {
