@@ -703,8 +703,9 @@ static int batch_args(fdas_plan_t pl, const SeriesDesc *d_desc, int nseries, int
 int plan_convolve_peaks(fdas_plan_t pl, const void *spec, int64_t nbins, float thr, void *work,
                         int64_t cand_cap, void *peaks, int64_t peak_cap,
                         unsigned long long *counts, hipStream_t s) {
-  hipError_t e = launch_peaks_reset(counts, s);
-  if (e != hipSuccess) return hip_error(e, "peak counter reset");
+  void *table = static_cast<unsigned char *>(work) + (size_t)cand_cap * sizeof(Cand);
+  hipError_t e = launch_peaks_clear(cand_cap, table, counts, s);
+  if (e != hipSuccess) return hip_error(e, "peak table reset");
   CandOut cd;
   cd.list = static_cast<Cand *>(work);
   cd.count = counts;
@@ -712,7 +713,6 @@ int plan_convolve_peaks(fdas_plan_t pl, const void *spec, int64_t nbins, float t
   cd.thr = thr;
   const int st = plan_launch(pl, spec, nbins, nullptr, 0, cd, s);
   if (st != FDAS_OK) return st;
-  void *table = static_cast<unsigned char *>(work) + (size_t)cand_cap * sizeof(Cand);
   e = launch_peaks(cd.list, cand_cap, table, counts, (pl->p.flags & FDAS_FLAG_INTERBIN) ? 1 : 0,
                    static_cast<Cand *>(peaks), peak_cap, s);
   if (e != hipSuccess) return hip_error(e, "peak kernels");
