@@ -533,12 +533,25 @@ static UnitSplit launch_split(fdas_plan_t pl, int64_t nsb) {
   return best;
 }
 
+// Whether a launch over nsb segment groups takes rows z and -z apart, one row
+// to a block: where that leaves a SIMD at most one wavefront (or a compute unit
+// one block of more than four) the time is that of one block, whose second
+// inverse transform is then its longest part. (FP32, 2048 points, 510 rows of
+// segments: 8.1 us against 9.3 as 255 pairs; 765: 9.8 both; 1010: 11.9 against
+// 9.9. FP16: 255 9.1 against 9.3, 303 13.0 against 9.5.)
+static bool rows_apart(fdas_plan_t pl, int64_t nsb) {
+  if (!pl->pair || pl->zpb_forced || plan_cus(pl) <= 0) return false;
+  const int waves = pl->var->T * pl->var->G / 64;
+  return nsb * pl->nz <= (int64_t)pl->cus * std::max(1, 4 / std::max(1, waves));
+}
+
 static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *power, int64_t ld,
                        const CandOut &cand, hipStream_t s) {
   const int64_t nseg = (nbins + pl->U - 1) / pl->U;
   if (nseg > INT_MAX / 2) return set_error(FDAS_ERR_UNSUPPORTED, "nbins %lld too large", (long long)nbins);
   const int64_t nsb = (nseg + pl->var->G - 1) / pl->var->G;
-  const UnitSplit split = launch_split(pl, nsb);
+  const bool apart = rows_apart(pl, nsb);
+  const UnitSplit split = apart ? UnitSplit{0, 1, 1} : launch_split(pl, nsb);
   pl->last_zpb = split.n1 ? split.zpb1 : split.zpb2;
   const int64_t nzg = (pl->nz + split.zpb2 - 1) / split.zpb2;
   if (nsb * nzg > (int64_t)UINT_MAX)
@@ -561,7 +574,7 @@ static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *p
   while ((1 << a.bank_log2) < pl->L) ++a.bank_log2;
   a.consts = pl->consts;
   a.cand = cand;
-  a.pair = pl->pair;
+  a.pair = apart ? 0 : pl->pair;
   hipError_t e = pl->var->launch(a, s);
   if (e != hipSuccess) return hip_error(e, "correlation kernel launch");
   return FDAS_OK;

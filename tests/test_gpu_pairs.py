@@ -70,3 +70,28 @@ def test_batches(gpu, monkeypatch, prec, L, m, flags, tol, persistent, zpb):
         outs = [o.cpu().numpy() for o in outs]
     for a, (n, z), o in zip(spectra, specs, outs):
         check(o, oracle.plane_direct(a, z, 2.0, m), n, tol)
+
+
+@pytest.mark.parametrize("prec,L,m,flags,tol", FORMS)
+def test_rows_apart_in_small_launches(gpu, monkeypatch, prec, L, m, flags, tol):
+    """On both sides of 256, 512 and 1024 rows of segments, the line of one
+    kernel or another between rows apart and pairs: the plane is within twice
+    the bar of the one made as pairs, and detection finds its points."""
+    import torch
+    zmax, rows = 16.0, 17
+    for blocks in (256, 512, 1024):
+        for nseg in (blocks // rows, blocks // rows + 1):
+            nbins = nseg * (L - m) - 3
+            a = to_dev(synth.small_random_spectrum(nbins, seed=nseg))
+            monkeypatch.delenv("FDAS_ZPB", raising=False)
+            with gpu.Plan(zmax, 2.0, m, L, prec, flags) as p:
+                out = p.convolve(a)
+                thr = float(out.flatten()[:: 7].median()) * 8
+                row, r, power = gpu.decode_candidates(*p.candidates(a, thr, capacity=rows * nbins))
+            monkeypatch.setenv("FDAS_ZPB", "2")
+            with gpu.Plan(zmax, 2.0, m, L, prec, flags) as p:
+                pairs = p.convolve(a)
+            assert float((out - pairs).abs().max()) <= 2 * tol * float(pairs.max())
+            out = out.cpu().numpy()
+            assert sorted(zip(row.tolist(), r.tolist())) == list(zip(*np.nonzero(out >= thr)))
+            assert np.array_equal(power, out[row, r])
