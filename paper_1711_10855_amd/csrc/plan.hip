@@ -503,6 +503,14 @@ static int plan_slots(fdas_plan_t pl) {
 // when the rest had done theirs: 195 us, against 173 with 256 whole units and
 // the other 18 segments in units of 8. 2^21 x 101 in FP32: 294 against 276 us.
 // 65536 bins in FP16, 18 segments on 512 slots: 61 against 16 us.)
+// A last round with fewer blocks on a compute unit than it holds ends sooner, in
+// proportion down to kAlone of a full one, where a block no longer shares its
+// SIMDs. (Alone against in full company, in units of like size: 1 : 1.5 at 4096
+// points in FP32, 1.64 at 2048, 2.1 at 1024, 1.6 in FP16. 19 segments of 4096
+// points and 33 rows: 323 units of 2 rows 17.6 us, 209 of 3 14.5. Not so after
+// whole rounds, whose blocks end one by one: 2^21 x 101 in FP32 283 us without
+// and 285 with it.)
+constexpr double kAlone = 0.65;
 struct UnitSplit {
   int64_t n1;
   int zpb1, zpb2;
@@ -520,9 +528,12 @@ static UnitSplit launch_split(fdas_plan_t pl, int64_t nsb) {
     for (int g = 1; g <= n; ++g) {
       const int per = (n + g - 1) / g;
       if (g > 1 && per == (n + g - 2) / (g - 1)) continue;  // the same units as before
-      const int64_t rounds = (rest * ((n + per - 1) / per) + slots - 1) / slots;
-      const double cost =
-          (double)k * (each * n + fwd) + (double)rounds * ((double)each * per + fwd);
+      const int64_t units = rest * ((n + per - 1) / per), left = units % slots;
+      double last = left ? 1.0 : 0.0;
+      if (left && k == 0)
+        last = std::max(kAlone, (double)((left + pl->cus - 1) / pl->cus) * pl->cus / slots);
+      const double rounds = (double)(units / slots) + last;
+      const double cost = (double)k * (each * n + fwd) + rounds * ((double)each * per + fwd);
       if (best_cost == 0.0 || cost < best_cost * 0.999) {
         best_cost = cost;
         best = {k * slots, pl->nz, std::min(each * per, pl->nz)};
@@ -632,7 +643,10 @@ static int series_desc(fdas_plan_t pl, const fdas_series &x, int i, SeriesDesc *
 // last round of the GPU's block slots: those in near-equal groups of at most
 // `zpb` templates, so that the blocks end together. The size is the one whose
 // work, spread over the slots, and half an item for the uneven end are least;
-// a batch of less than a round is all tail. (12 series of 2^19 .. 2^21 bins and
+// a batch of less than a round is all tail, and its blocks run in rounds as
+// those of a single spectrum do. (5 series of 20 segments and 201 rows in FP32
+// on 512 slots: items of 34 rows, 0.82 rounds, 110 us; of 26, 1.09, 137; of 14,
+// 2.05, 112. 12 series of 2^19 .. 2^21 bins and
 // 33 .. 101 rows in FP32: 1302 us in groups of at most 40 rows, 1257 this way; 6
 // series of 95000 .. 190000 bins in FP16: 116 against 86 us.) FDAS_ZPB or the
 // autotuner fixes one size for all. get(k): segment groups and rows of the
@@ -658,15 +672,25 @@ static BatchUnits batch_units(fdas_plan_t pl, int n, Get &&get) {
   for (int k = 0; k < tail; ++k) head += (double)get(k).first * (get(k).second + fwd);
   BatchUnits best{tail, tail_rows};
   double best_time = 0.0;
-  for (int groups : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+  for (int groups : {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32}) {
     int zpb = (tail_rows + groups - 1) / groups;
     if (pl->pair) zpb += zpb & 1;
     work = head;
+    int64_t units = 0;
+    int longest = 0;
     for (int k = tail; k < n; ++k) {
       const auto x = get(k);
-      work += (double)x.first * (x.second + fwd * ((x.second + zpb - 1) / zpb));
+      const int ng = (x.second + zpb - 1) / zpb;
+      work += (double)x.first * (x.second + fwd * ng);
+      units += x.first * ng;
+      longest = std::max(longest, (x.second + ng - 1) / ng);
     }
-    const double item = zpb + fwd, time = std::max(item, work / slots + 0.5 * item);
+    double time = std::max(zpb + fwd, work / slots + 0.5 * (zpb + fwd));
+    if (tail == 0) {
+      const double full = std::floor(units / slots), left = units - full * slots;
+      time = (longest + fwd) *
+             (full + (left > 0.0 ? std::max(kAlone, std::ceil(left / pl->cus) * pl->cus / slots) : 0.0));
+    }
     if (best_time == 0.0 || time < best_time * 0.999) {
       best_time = time;
       best.zpb = zpb;
