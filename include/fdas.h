@@ -148,7 +148,7 @@ int fdas_resolve_params(const fdas_params *in, fdas_params *out);
  *               overlap-and-save product multiplies by instead, device
  *               complex64 [nz][L] in natural frequency order,
  *               T_i[k] = conj(sum_q H_{z_i}(q) exp(-2 pi i (q mod L) k / L)) / L
- *               (an FP64 direct sum with exact phase reduction, rounded to
+ *               (FP64 sums over the taps q and -q together, rounded to
  *               FP32; L = seg_len as resolved, which must not be left to the
  *               autotuner). This form allocates an FP64 temporary of
  *               nz (m+1) 16 bytes and synchronises `stream`.
@@ -237,10 +237,11 @@ int fdas_convolve_peaks(fdas_plan_t plan, const void *spectrum, int64_t nbins, f
  * at once take items from a device counter (reset by a kernel in the same
  * graph) until none is left. FDAS_BATCH_PERSISTENT=0 in the environment
  * selects a flat grid of one block per item instead. Each series uses the
- * central rows of the plan's bank; a batch that fills the GPU many times over
- * gives each (series, segment) one work item for all its templates. The
- * launch is captured once into a HIP graph per distinct batch shape and
- * replayed. `series` is host memory with nseries >= 1 entries.               */
+ * central rows of the plan's bank; a (series, segment) is one work item for
+ * all its templates, but for the series that make up the last round of blocks,
+ * whose templates are split so that the blocks end together. The launch is
+ * captured once into a HIP graph per distinct batch shape and replayed.
+ * `series` is host memory with nseries >= 1 entries.                         */
 int fdas_convolve_batch(fdas_plan_t plan, const fdas_series *series,
                         int nseries, void *stream);
 

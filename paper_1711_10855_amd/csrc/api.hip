@@ -514,7 +514,8 @@ int fdas_frontend_plan(fdas_frontend_t *out, int64_t n, int device, void *stream
     g.N2 = 1 << (lg / 2);
   }
   int st = find_fft(g.N1, 0, &g.f1);
-  if (st == FDAS_OK && g.N2 > 1) st = find_fft(g.N2, 0, &g.f2);
+  const FftVariant *second = nullptr;
+  if (st == FDAS_OK && g.N2 > 1) st = find_fft(g.N2, 0, &second);
   if (st != FDAS_OK) return st;
   int ndev = 0;
   hipError_t e = hipGetDeviceCount(&ndev);

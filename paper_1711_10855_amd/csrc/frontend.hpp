@@ -15,15 +15,14 @@ namespace fdas {
 struct FrontendGeom {
   int64_t M;
   int N1, N2;
-  const FftVariant *f1, *f2;
+  const FftVariant *f1;  // the one transform when N2 == 1
   const c32 *tw1, *tw2;  // twiddle tables of lengths N1 and N2: W_N1^j, or with
                          // N2 > 1 the stage tables of both
 };
 
 size_t frontend_sel_bytes();
 // The twiddles of the n-point transforms of an M-point one (at most n entries
-// each) in the order their
-// stages read them: for each stage, factor k of suffix mi at (k - 1) S + mi, so
+// each) in the order their stages read them: for each stage, factor k of suffix mi at (k - 1) S + mi, so
 // that consecutive threads read consecutive entries. (Picked out of W_n^j one
 // load of a wave touches up to 60 lines.)
 hipError_t launch_stage_table(c32 *out, int n, int64_t M, const c32 *tw, hipStream_t s);

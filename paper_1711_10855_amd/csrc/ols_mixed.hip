@@ -1166,9 +1166,7 @@ static OlsVariant make_mixed(const char *name, int precision) {
   v.precision = precision;
   v.split = SPLIT ? 1 : 0;
   v.pair = PF == 5;
-  // The forward FFT costs several templates' worth of time here; units of
-  // up to 72 templates with a shorter last group measured fastest (17 to 101
-  // swept on the paper-scale plane).
+  // The forward FFT costs several templates' worth of time here.
   v.zpb_target = 72;
   v.unit_cost = SPLIT ? 5.0f : 8.0f;
   v.lay.L = 4096;

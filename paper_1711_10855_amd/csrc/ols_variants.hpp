@@ -199,8 +199,8 @@ struct OlsVariant {
   int precision;     // FDAS_FP32 (0), FDAS_MIXED_FP16 (1), FDAS_MIXED_BF16 (2)
   int split;         // 1: hi + lo split products (FDAS_FLAG_SPLIT)
   int pair;          // 1: has a pair form, used where the bank's rows mirror
-  int zpb_target;    // > 0: templates per work item of a batch that does not fill
-                     // the GPU many times over; 0: near-equal groups of at most 40
+  int zpb_target;    // templates per unit where the size of the GPU is not known:
+                     // units of that many, or (0) near-equal ones of at most 40
   float unit_cost;   // what a unit's forward transform takes, in templates
   LayoutDesc lay;
   int lds_bytes;

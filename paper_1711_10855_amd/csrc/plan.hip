@@ -79,14 +79,12 @@ static const OlsVariant *find_variant(int L, int precision, int split, const cha
 
 constexpr int kFp32UnitTarget = 40;
 
-// Templates per work unit. Without a target (plans that choose per launch;
-// batched launches split each series this way), near-equal groups of at
-// most 40 (larger groups ran 2.7% faster on the 512-series batch than ~32). With a target: units of `target` templates
-// in group order and the remainder last (a remainder under a third of the
-// target is spread over the other groups), and fewer rows than the target
-// split about 3 : 1; work units are dispatched in group order, so the short
-// ones start last and fill the end of the launch (on the 2^21-bin plane this
-// measured 3-6% faster than equal groups at 65, 101 and 201 rows).
+// Templates per work unit where the number of block slots is not known (and what
+// plan info reports before a launch). Without a target, near-equal groups of at
+// most 40. With one: units of `target` templates in group order and the
+// remainder last (a remainder under a third of the target is spread over the
+// other groups), and fewer rows than the target split about 3 : 1, so that the
+// short units, dispatched last, fill the end of the launch.
 static int default_zpb(int nz, int target) {
   if (target <= 0) {
     const int groups = (nz + kFp32UnitTarget - 1) / kFp32UnitTarget;

@@ -220,7 +220,7 @@ def make_templates(zmax, dz, m=0, flags=0):
 
 def make_bank(zmax, dz, m=0, seg_len=0, flags=0):
     """The Fourier-domain template bank T_i[k], complex64 tensor [rows, L] in
-    natural frequency order on the current device (FP64 direct sums rounded
+    natural frequency order on the current device (FP64 sums rounded
     to FP32; fdas_make_templates with FLAG_BANK)."""
     import torch
     p = params(zmax, dz, m, seg_len, "fp32", flags | FLAG_BANK)
