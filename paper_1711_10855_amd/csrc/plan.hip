@@ -242,8 +242,7 @@ static int autotune(const fdas_params &p, int nz, int device, hipStream_t s, Tun
       const OlsVariant *v = &vs[i];
       if (v->precision != p.precision || v->split != plan_split(p)) continue;
       if (p.seg_len ? v->L != p.seg_len : (v->L - p.m) * 2 < v->L) continue;
-      // zpb 0: the plan's own choice (units of the variant's target size, or
-      // per launch from the grid's rounds); then fixed near-equal groups
+      // zpb 0: the plan's own choice, per launch; then fixed near-equal groups
       std::vector<int> cands = {0};
       for (int ng : {1, 2, 3, 4, 6, 8, 12}) {
         const int zpb = (nz + ng - 1) / ng;
