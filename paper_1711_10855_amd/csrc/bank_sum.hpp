@@ -14,9 +14,16 @@
 //
 // The angle is reduced exactly (q k mod L) and its cosine read from a
 // quarter-wave table in LDS, which the block makes once with sincospi; a wave
-// holds kBankRows rows of 64 frequencies in registers, so one table read
-// serves them all. One sincospi per term and frequency instead took 227 us
-// for 101 rows of 2048 frequencies (257 taps), against 20 us.
+// holds ROWS rows of 64 frequencies in registers, so one table read serves them
+// all. One sincospi per term and frequency instead took 227 us for 101 rows of
+// 2048 frequencies (257 taps), against 12 us.
+//
+// ROWS is 4 where that makes more blocks than the 256 compute units, and 2
+// below, where the chip is not full and the chains of table reads and of taps
+// from memory bound it: half the rows, and twice the taps staged and table reads
+// in flight at a time. (101 rows of 2048: 19.9 us with 4, 11.6 with 2. The whole
+// call for 201 rows of 4096, 513 taps, 231 blocks of 4: 67 against 62 us; of
+// 8192, 455 blocks: 79 against 82.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -27,24 +34,23 @@ struct c64b {
   double x, y;
 };
 
-constexpr int kBankRows = 4;    // rows per wave
 constexpr int kBankWaves = 4;   // waves per block, on different rows
-constexpr int kBankTaps = 32;   // taps staged in LDS at a time
 
 // put(row, k, re, im) stores S = (re, im) of bank row `row` at frequency k.
 // h holds the templates [rows][m + 1]; nzg counts the rows of the z grid.
-template <bool HALF, class Put>
+template <bool HALF, int ROWS, class Put>
 __global__ void __launch_bounds__(64 * kBankWaves)
     bank_sum_kernel(const c64b *__restrict__ h, int nzg, int interbin, int m, int L, Put put) {
+  constexpr int kBankTaps = 128 / ROWS;  // staged in LDS at a time
   extern __shared__ double cos_tab[];  // cos(2 pi j / L), j in [0, L / 4]
-  __shared__ c64b even[kBankWaves * kBankRows][kBankTaps];
-  __shared__ c64b odd[HALF ? kBankWaves * kBankRows : 1][kBankTaps];
+  __shared__ c64b even[kBankWaves * ROWS][kBankTaps];
+  __shared__ c64b odd[HALF ? kBankWaves * ROWS : 1][kBankTaps];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int quarter = L >> 2, half_m = m >> 1;
   for (int j = tid; j <= quarter; j += 64 * kBankWaves) cos_tab[j] = cospi(2.0 * (double)j / (double)L);
   const int k = blockIdx.x * 64 + lane;  // up to L / 2
   const int rows = HALF ? nzg : (nzg + 1) >> 1;
-  const int r0 = blockIdx.y * (kBankWaves * kBankRows);
+  const int r0 = blockIdx.y * (kBankWaves * ROWS);
   auto row_of = [&](int r) { return interbin ? 2 * r + (HALF ? 1 : 0) : r; };
   auto cosine = [&](int j) {  // cos(2 pi j / L), j in [0, L)
     j = j > L / 2 ? L - j : j;
@@ -52,10 +58,10 @@ __global__ void __launch_bounds__(64 * kBankWaves)
     const double c = cos_tab[neg ? L / 2 - j : j];
     return neg ? -c : c;
   };
-  double pr[kBankRows], pi[kBankRows], qr[kBankRows], qi[kBankRows];
+  double pr[ROWS], pi[ROWS], qr[ROWS], qi[ROWS];
 #pragma unroll
-  for (int i = 0; i < kBankRows; ++i) {
-    const int r = r0 + w * kBankRows + i;
+  for (int i = 0; i < ROWS; ++i) {
+    const int r = r0 + w * ROWS + i;
     pr[i] = pi[i] = qr[i] = qi[i] = 0.0;
     if (r < rows) {
       const c64b v = h[(long)row_of(r) * (m + 1) + half_m];
@@ -66,7 +72,7 @@ __global__ void __launch_bounds__(64 * kBankWaves)
   for (int q0 = 1; q0 <= half_m; q0 += kBankTaps) {
     const int n = min(kBankTaps, half_m + 1 - q0);
     __syncthreads();  // the table is made; the taps before have been read
-    for (int i = tid; i < kBankWaves * kBankRows * kBankTaps; i += 64 * kBankWaves) {
+    for (int i = tid; i < kBankWaves * ROWS * kBankTaps; i += 64 * kBankWaves) {
       const int r = r0 + i / kBankTaps, q = q0 + i % kBankTaps;
       c64b a = {0.0, 0.0}, b = {0.0, 0.0};
       if (r < rows && q <= half_m) {
@@ -78,19 +84,19 @@ __global__ void __launch_bounds__(64 * kBankWaves)
       if constexpr (HALF) odd[i / kBankTaps][i % kBankTaps] = {a.x - b.x, a.y - b.y};
     }
     __syncthreads();
-#pragma unroll 4
+#pragma unroll (16 / ROWS)
     for (int t = 0; t < n; ++t) {
       const int j = (int)(((unsigned)(q0 + t) * (unsigned)k) & (unsigned)(L - 1));
       const double c = cosine(j);
       double sn = 0.0;
       if constexpr (HALF) sn = cosine((j + 3 * quarter) & (L - 1));
 #pragma unroll
-      for (int i = 0; i < kBankRows; ++i) {
-        const c64b s = even[w * kBankRows + i][t];
+      for (int i = 0; i < ROWS; ++i) {
+        const c64b s = even[w * ROWS + i][t];
         pr[i] = __builtin_fma(s.x, c, pr[i]);
         pi[i] = __builtin_fma(s.y, c, pi[i]);
         if constexpr (HALF) {
-          const c64b d = odd[w * kBankRows + i][t];
+          const c64b d = odd[w * ROWS + i][t];
           qr[i] = __builtin_fma(d.x, sn, qr[i]);
           qi[i] = __builtin_fma(d.y, sn, qi[i]);
         }
@@ -100,8 +106,8 @@ __global__ void __launch_bounds__(64 * kBankWaves)
   if (k > L / 2) return;
   const int mk = (L - k) & (L - 1);
 #pragma unroll
-  for (int i = 0; i < kBankRows; ++i) {
-    const int r = r0 + w * kBankRows + i;
+  for (int i = 0; i < ROWS; ++i) {
+    const int r = r0 + w * ROWS + i;
     if (r >= rows) continue;
     // P - i Q at k, P + i Q at L - k
     put(row_of(r), k, pr[i] + qi[i], pi[i] - qr[i]);
@@ -113,20 +119,31 @@ __global__ void __launch_bounds__(64 * kBankWaves)
   }
 }
 
+template <bool HALF, class Put>
+static void launch_bank_part(const void *h, int nzg, int interbin, int m, int L, Put put,
+                             hipStream_t s) {
+  const int rows = HALF ? nzg : (nzg + 1) / 2;
+  const unsigned gx = (unsigned)(L / 2 / 64 + 1);
+  const size_t lds = (size_t)(L / 4 + 1) * sizeof(double);
+  auto blocks = [&](int per_wave) {
+    return dim3(gx, (unsigned)((rows + kBankWaves * per_wave - 1) / (kBankWaves * per_wave)));
+  };
+  const dim3 wide = blocks(4);
+  if (wide.x * wide.y > 256)
+    hipLaunchKernelGGL((bank_sum_kernel<HALF, 4, Put>), wide, dim3(64 * kBankWaves), lds, s,
+                       static_cast<const c64b *>(h), nzg, interbin, m, L, put);
+  else
+    hipLaunchKernelGGL((bank_sum_kernel<HALF, 2, Put>), blocks(2), dim3(64 * kBankWaves), lds, s,
+                       static_cast<const c64b *>(h), nzg, interbin, m, L, put);
+}
+
 // Every row of a bank: `rows` counts bank rows (twice the z grid with interbin).
 template <class Put>
 static hipError_t launch_bank_sum(const void *h, int rows, int interbin, int m, int L, Put put,
                                   hipStream_t s) {
   const int nzg = interbin ? rows / 2 : rows;
-  const unsigned gx = (unsigned)(L / 2 / 64 + 1), per = kBankWaves * kBankRows;
-  const size_t lds = (size_t)(L / 4 + 1) * sizeof(double);
-  hipLaunchKernelGGL((bank_sum_kernel<false, Put>), dim3(gx, ((nzg + 1) / 2 + per - 1) / per),
-                     dim3(64 * kBankWaves), lds, s, static_cast<const c64b *>(h), nzg, interbin, m,
-                     L, put);
-  if (interbin)
-    hipLaunchKernelGGL((bank_sum_kernel<true, Put>), dim3(gx, (nzg + per - 1) / per),
-                       dim3(64 * kBankWaves), lds, s, static_cast<const c64b *>(h), nzg, interbin,
-                       m, L, put);
+  launch_bank_part<false>(h, nzg, interbin, m, L, put, s);
+  if (interbin) launch_bank_part<true>(h, nzg, interbin, m, L, put, s);
   return hipGetLastError();
 }
 

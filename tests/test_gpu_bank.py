@@ -31,3 +31,12 @@ def test_bank_sums(gpu, prec, L, m, zmax, dz, flags):
     assert np.max(np.abs(bank.astype(np.complex128) - ref)) <= tol * np.max(np.abs(ref))
     whole = bank[0::2] if interbin else bank
     assert np.array_equal(whole, whole[::-1].conj())
+
+
+@pytest.mark.parametrize("m", [34, 130, 256])
+@pytest.mark.parametrize("zmax,flags", [(31.0, 0), (32.0, 0), (15.0, 4), (16.0, 4)])
+def test_bank_sums_on_both_sides_of_a_full_chip(gpu, m, zmax, flags):
+    """At L 16384 (129 blocks a tile of rows) 32 and 33 rows, or 16 and 17 at
+    half-bin offsets, lie on the two sides of 256 blocks: two rows to a wave
+    and four."""
+    test_bank_sums(gpu, "fp32", 16384, m, zmax, 2.0, flags)
