@@ -5,6 +5,7 @@
 
 #include <cstdint>
 
+#include "cand_place.hpp"
 #include "fft_radix.hpp"
 #include "layout.hpp"
 
@@ -32,9 +33,8 @@ struct CandOut {
 // that the launch waits for (2^21 bins x 101 rows in FP32 with eight signals,
 // against 223 us without a hit: 276 us with a global atomic per power, 254 with
 // one per template and wave, 228 collected).
-constexpr int kCandLds = 320;
 struct CandLds {
-  int n;    // entries asked for; from `lim` on they did not fit
+  int n;    // entries asked for (see cand_place); from `lim` on they did not fit
   int lim;
   unsigned long long base;
   struct {
@@ -73,9 +73,13 @@ __device__ __forceinline__ void cand_offer(const CandOut &cd, CandLds *b, int ro
   if (total == 0) return;
   const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   int pos = 0;
-  if (lane == 0) pos = atomicAdd(&b->n, total);
+  if (lane == 0)
+    pos = cand_place(
+        total,
+        [&] { return __hip_atomic_load(&b->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); },
+        [&](int k) { return atomicAdd(&b->n, k); });
   pos = __builtin_amdgcn_readfirstlane(pos);
-  const bool fits = pos + total <= kCandLds;
+  const bool fits = cand_fits(pos, total);
   unsigned long long base = 0ull;
   if (!fits) {  // straight to the list
     if (lane == 0) {
@@ -107,7 +111,7 @@ __device__ __forceinline__ void cand_offer(const CandOut &cd, CandLds *b, int ro
 // in the offers.
 __device__ __forceinline__ void cand_end(const CandOut &cd, CandLds *b, int64_t r0) {
   __syncthreads();
-  const int m = b->n < b->lim ? b->n : b->lim;
+  const int m = cand_listed(b->n, b->lim);
   if (m == 0) return;
   if (threadIdx.x == 0) b->base = atomicAdd(cd.count, (unsigned long long)m);
   __syncthreads();
