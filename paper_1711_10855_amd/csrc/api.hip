@@ -527,8 +527,9 @@ int fdas_frontend_plan(fdas_frontend_t *out, int64_t n, int device, void *stream
   if (!p) return set_error(FDAS_ERR_NOMEM, "host allocation");
   p->device = device;
   p->n = n;
-  e = hipMalloc(&p->tw1, (size_t)g.N1 * sizeof(c32));
-  if (e == hipSuccess && g.N2 > 1) e = hipMalloc(&p->tw2, (size_t)g.N2 * sizeof(c32));
+  const size_t per = g.N2 > 1 ? kStageTableEntries * sizeof(c32) : sizeof(c32);
+  e = hipMalloc(&p->tw1, (size_t)g.N1 * per);
+  if (e == hipSuccess && g.N2 > 1) e = hipMalloc(&p->tw2, (size_t)g.N2 * per);
   if (e == hipSuccess) e = hipMalloc(&p->work, (size_t)M * sizeof(c32));
   if (e == hipSuccess) e = hipMalloc(&p->pw, (size_t)M * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&p->sel, frontend_sel_bytes());
@@ -539,11 +540,9 @@ int fdas_frontend_plan(fdas_frontend_t *out, int64_t n, int device, void *stream
   const hipStream_t s = static_cast<hipStream_t>(stream);
   if (g.N2 == 1) {
     e = launch_twiddles(p->tw1, g.N1, s);
-  } else {  // (the work buffer, M >= N1 entries, holds each plain table meanwhile)
-    e = launch_twiddles(p->work, g.N1, s);
-    if (e == hipSuccess) e = launch_stage_table(p->tw1, g.N1, M, p->work, s);
-    if (e == hipSuccess) e = launch_twiddles(p->work, g.N2, s);
-    if (e == hipSuccess) e = launch_stage_table(p->tw2, g.N2, M, p->work, s);
+  } else {
+    e = launch_stage_table(p->tw1, g.N1, M, s);
+    if (e == hipSuccess) e = launch_stage_table(p->tw2, g.N2, M, s);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) {

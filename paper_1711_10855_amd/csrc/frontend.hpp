@@ -21,11 +21,13 @@ struct FrontendGeom {
 };
 
 size_t frontend_sel_bytes();
-// The twiddles of the n-point transforms of an M-point one (at most n entries
-// each) in the order their stages read them: for each stage, factor k of suffix mi at (k - 1) S + mi, so
+// The twiddles of the n-point transforms of an M-point one in the order their
+// stages read them: for each stage, factor k of suffix mi at (k - 1) S + mi, so
 // that consecutive threads read consecutive entries. (Picked out of W_n^j one
-// load of a wave touches up to 60 lines.)
-hipError_t launch_stage_table(c32 *out, int n, int64_t M, const c32 *tw, hipStream_t s);
+// load of a wave touches up to 60 lines.) At most n factors; those of short
+// series come with their rounding errors, two entries each.
+constexpr int kStageTableEntries = 2;
+hipError_t launch_stage_table(c32 *out, int n, int64_t M, hipStream_t s);
 hipError_t launch_frontend(const FrontendGeom &g, const float *series, c32 *spectrum, c32 *work,
                            float *pw, void *sel, float *stats, hipStream_t s);
 
