@@ -51,6 +51,24 @@ __device__ __forceinline__ T *uniform_ptr(T *p) {
   return reinterpret_cast<T *>(((uint64_t)hi << 32) | lo);
 }
 
+// Whether segments narrower than a wave (256 points) are stored past the L2.
+// Their pieces of 128 bytes are then best whole lines: at 64-byte alignment 130
+// rows x 2^21 bins take 329 us, 381 through the L2. Where the rows or the
+// segments lie otherwise each piece ends inside lines, which the L2 has to put
+// together before they leave it (rows off by 4 bytes: 667 against 438 us; m = 50:
+// 807 against 419), unless the caches behind it still do (rows off by 4, 17 rows
+// x 2^18 bins, 18 MB: 11.9 against 12.1 us; 65 rows, 68 MB: 41 against 27). The
+// smallest planes stay in the L2 (17 rows x 2^14: 5.2 against 4.6 us; from 4 MB on
+// the two are even). A series of a batch says nothing of how much is written
+// with it: there, lines alone decide.
+__device__ __forceinline__ bool narrow_nontemporal(const float *power, int64_t ld, int rows, int U,
+                                                   int half, bool batch) {
+  const int64_t bytes = ld * rows * 4;
+  const bool lines = ((reinterpret_cast<uint64_t>(power) | (uint64_t)(ld * 4)) & 63) == 0;
+  if (((U | half) & 15) != 0) return false;
+  return batch ? lines : bytes >= (4 << 20) && (lines || bytes <= (18 << 20));
+}
+
 // One work unit: segment s of a spectrum, bank rows [z0, z1), plane rows
 // (iz - row_base). The unit starts on LDS buffer 0: its caller guarantees a
 // block barrier since any earlier unit's last LDS read.
@@ -62,7 +80,8 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
                                          float *__restrict__ power_, int64_t ld, int s, bool active,
                                          int U, int half, int z0, int z1, int row_base, int rows,
                                          c32 *buf0, c32 *buf1, int t, const CandOut &cd,
-                                         CandLds *found = nullptr, int s_first = 0) {
+                                         CandLds *found = nullptr, int s_first = 0,
+                                         bool batch = false) {
   const auto spec = to_global(spec_);
   const auto bank = to_global(bank_);
   const auto tw = to_global(tw_);
@@ -205,23 +224,26 @@ __device__ __forceinline__ void ols_unit(const c32 *__restrict__ spec_, int64_t 
         }
     } else if (active) {
       // Segments narrower than a wave: per-lane addresses, in pieces of 4 T
-      // bytes. Where rows are not 128-byte aligned the pieces end inside
-      // lines, which the L2 has to put together before they leave it: these
-      // stores are not nontemporal (2097151 bins x 51 rows at 256 points: 145
-      // against 251 us; aligned rows are no slower).
+      // bytes (see narrow_nontemporal).
       constexpr int S0 = Gm::S(0), R0 = Gm::R[0];
       const auto prow = power + (int64_t)(iz - row_base) * ld;
+      auto store = [&](auto put) {
 #pragma unroll
-      for (int j = 0; j < Gm::B(0); ++j)
+        for (int j = 0; j < Gm::B(0); ++j)
 #pragma unroll
-        for (int n = 0; n < R0; ++n) {
-          const int o = n * S0 + t + j * T;
-          const int64_t r = (int64_t)s * U + o - half;
-          if (o >= half && o < half + U && r < nbins) {
-            const c32 v = y[j * R0 + n];
-            prow[r] = __builtin_fmaf(v.x, v.x, v.y * v.y);
+          for (int n = 0; n < R0; ++n) {
+            const int o = n * S0 + t + j * T;
+            const int64_t r = (int64_t)s * U + o - half;
+            if (o >= half && o < half + U && r < nbins) {
+              const c32 v = y[j * R0 + n];
+              put(prow + r, __builtin_fmaf(v.x, v.x, v.y * v.y));
+            }
           }
-        }
+      };
+      if (narrow_nontemporal(power_, ld, rows, U, half, batch))
+        store([](auto to, float p) { __builtin_nontemporal_store(p, to); });
+      else
+        store([](auto to, float p) { *to = p; });
     }
   };
 
@@ -444,7 +466,7 @@ __global__ void __launch_bounds__(Gm::T *G) __attribute__((amdgpu_waves_per_eu(W
     ols_unit<Gm, TWREG, PF, false, PAIR>(static_cast<const c32 *>(d.spec), d.nbins,
                                          opaque_ptr(bank), opaque_ptr(tw), d.power, d.ld, s,
                                          s < d.nseg, U, half, z0, z1, d.row_off, d.nz, lds[0][sg],
-                                         lds[NB - 1][sg], t, none);
+                                         lds[NB - 1][sg], t, none, nullptr, 0, true);
   }
 }
 
@@ -481,7 +503,7 @@ __global__ void __launch_bounds__(Gm::T *G) __attribute__((amdgpu_waves_per_eu(W
   const CandOut none{};
   ols_unit<Gm, TWREG, PF, false, PAIR>(static_cast<const c32 *>(d.spec), d.nbins, bank, tw, d.power,
                                        d.ld, s, s < d.nseg, U, half, z0, z1, d.row_off, d.nz,
-                                       lds[0][sg], lds[NB - 1][sg], t, none);
+                                       lds[0][sg], lds[NB - 1][sg], t, none, nullptr, 0, true);
 }
 
 __global__ void reset_counter_kernel(unsigned long long *counter) { *counter = 0ULL; }
