@@ -1,0 +1,125 @@
+// How a single-spectrum launch is cut into work units. Plain C++: the choice
+// also runs on the host.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+namespace fdas {
+
+// What the time of a launch depends on, in templates of one row in full company
+// (every slot of the GPU's blocks taken): see UnitCost.
+struct UnitModel {
+  double forward;  // a unit's forward transform
+  double alone;    // a block's time alone, as a share of that in full company
+  double fixed;    // the share that does not shrink with fewer blocks around it
+  double step;     // how far blocks keep step (1: in rounds, 0: as slots fall free)
+  double single;   // a row of the single form against one of the pair form
+};
+
+// Units of a launch: every row of the first n1 segment groups, then zpb2 rows at
+// a time of the others (zpb1 rows where n1 is given; see UnitGrid).
+struct UnitSplit {
+  int64_t n1;
+  int zpb1, zpb2;
+  int pair;  // rows z and -z together
+};
+
+// Estimated time of a launch over nsb segment groups, n1 of them in whole-row
+// units that fill k rounds of the `slots` block slots, the others in groups of
+// `per` of the n rows (or pairs of rows) each.
+//
+// Two limits bound it. Blocks that start together and are alike end together,
+// so that a launch runs in rounds as long as a unit; a last round with fewer
+// blocks ends sooner, as a block shares its SIMDs with fewer others, down to
+// `alone` of its time (by whole blocks on a compute unit). Blocks that drift
+// apart fill the slots as they fall free: the time is that of all the work
+// spread over the slots, and a share of one unit for the end. Which one it is
+// differs by kernel: blocks of one wave share a SIMD four ways and drift, a
+// block of 16 waves holds half a compute unit and keeps step.
+// The constants are fitted to measured times of 5 numbers of rows (17 .. 201) x
+// 9 lengths (15000 .. 2^21 bins) in up to 50 layouts each; what the estimate
+// picks takes on average 1.01 times the fastest of them at 256 and 512 points,
+// 1.004 times at the others. (256 points, 202 rows of single form, 1366 groups
+// on 4096 slots: units of 202 rows 203 us, 101 150, 41 140, 21 137, 9 155. 2048
+// points, 101 rows, 140 segments on 1024 slots: units of 102 rows 162 us, 22
+// 46.8, 16 43.0, 14 44.0, 12 52.7, 2 82.6. Units counted in whole rounds alone,
+// with one size for the end of a launch, took 1.33 times as long at worst: 102
+// rows x 1100000 bins at 256 points 187 us, where units of 34 rows take 141.)
+struct UnitCost {
+  UnitModel m;
+  int64_t nsb, slots;
+  int cus, nz, each;  // each: rows counted by one of n
+
+  double operator()(int64_t k, int per) const {
+    const int n = (nz + each - 1) / each, groups = (n + per - 1) / per;
+    const double rest = (double)(nsb - k * slots), units = rest * groups;
+    const double full = (double)(int64_t)(units / (double)slots);
+    const double left = units - full * (double)slots;
+    const double all = nz + m.forward;
+    const double unit = rest == 0.0 ? all : std::min(each * per, nz) + m.forward;
+    const double work = rest / (double)slots * (nz + m.forward * groups) + (double)k * all;
+    const double spread = std::max(m.alone * unit, m.fixed * unit + (1.0 - m.fixed) * work);
+    double last = 0.0;
+    if (left > 0.0) {
+      const double share = (double)(int64_t)((left + cus - 1) / cus) * cus / (double)slots;
+      last = std::max(m.alone, m.fixed + (1.0 - m.fixed) * share);
+    }
+    const double rounds = (double)k * all + (full + last) * unit;
+    return (double)slots * (m.step * rounds + (1.0 - m.step) * spread);
+  }
+
+  // No layout of k whole-row rounds and `groups` or more groups costs less.
+  double least(int64_t k, int groups) const {
+    const double work = (double)(nsb - k * slots) * (nz + m.forward * groups) +
+                        (double)(k * slots) * (nz + m.forward);
+    return (1.0 - m.fixed * (1.0 - m.step)) * work;
+  }
+};
+
+// The cheapest of: no whole-row units, or as many rounds of them as the groups
+// fill, or one less, and the rest in any number of near-equal row groups; in the
+// pair form (pair_slots > 0) or, without whole-row units, in the single form,
+// whose units may have an odd number of rows. Only layouts that can be the
+// cheapest are looked at: of those whose blocks all run alone the finest, and
+// then finer ones until the forward transforms alone cost more. `looked`, if
+// given, counts them.
+inline UnitSplit pick_units(const UnitModel &m, int64_t nsb, int nz, int cus, int64_t pair_slots,
+                            int64_t single_slots, int64_t *looked = nullptr) {
+  UnitSplit best{0, nz, nz, pair_slots > 0};
+  double best_cost = -1.0;
+  const double few = m.fixed < 1.0 ? std::max(0.0, (m.alone - m.fixed) / (1.0 - m.fixed)) : 0.0;
+  for (int pair = pair_slots > 0 ? 1 : 0; pair >= 0; --pair) {
+    const int64_t slots = pair ? pair_slots : single_slots;
+    if (slots <= 0) continue;
+    const double factor = pair_slots > 0 && !pair ? m.single : 1.0;
+    const UnitCost cost{m, nsb, slots, cus, nz, pair ? 2 : 1};
+    const int n = (nz + cost.each - 1) / cost.each;
+    // (the single form of a plan with pairs: without whole-row units only)
+    const int64_t full = pair || pair_slots <= 0 ? nsb / slots : 0;
+    for (int64_t k = full;; k = k == full && full > 1 ? full - 1 : 0) {
+      const int64_t rest = nsb - k * slots;
+      int64_t g = 1;
+      if (k == 0 && rest > 0)
+        g = std::max<int64_t>(1, (int64_t)(few * (double)slots / cus) * cus / rest);
+      g = std::min<int64_t>(g, n);
+      for (int per = (int)((n + g - 1) / g);;) {
+        const int groups = (n + per - 1) / per;
+        if (best_cost >= 0.0 && factor * cost.least(k, groups) >= best_cost) break;
+        const double c = factor * cost(k, per);
+        if (looked) ++*looked;
+        if (best_cost < 0.0 || c < best_cost * 0.999) {
+          best_cost = c;
+          best = {k * slots, nz, std::min(cost.each * per, nz), pair};
+        }
+        if (per == 1 || rest == 0) break;
+        const int next = (n + per - 2) / (per - 1);  // fewest groups of less than per
+        per = (n + next - 1) / next;
+      }
+      if (k == 0) break;
+    }
+  }
+  return best;
+}
+
+}  // namespace fdas

@@ -588,16 +588,17 @@ static int batch_blocks_per_cu(int pair) {
 }
 
 template <class Gm, int G, bool TWREG, bool PF, int WPE, int PWPE>
-static int grid_blocks_per_cu(int pair) {
+static int grid_blocks_per_cu(int pair, int detect) {
+  const void *kernel =
+      detect ? reinterpret_cast<const void *>(&ols_fp32_kernel<Gm, G, TWREG, PF, WPE, true, false>)
+             : reinterpret_cast<const void *>(&ols_fp32_kernel<Gm, G, TWREG, PF, WPE, false, false>);
   if constexpr (PWPE > 0) {
     if (pair)
-      return blocks_per_cu(
-          reinterpret_cast<const void *>(&ols_fp32_kernel<Gm, G, TWREG, PF, PWPE, false, true>),
-          Gm::T * G);
+      kernel =
+          detect ? reinterpret_cast<const void *>(&ols_fp32_kernel<Gm, G, TWREG, PF, PWPE, true, true>)
+                 : reinterpret_cast<const void *>(&ols_fp32_kernel<Gm, G, TWREG, PF, PWPE, false, true>);
   }
-  return blocks_per_cu(
-      reinterpret_cast<const void *>(&ols_fp32_kernel<Gm, G, TWREG, PF, WPE, false, false>),
-      Gm::T * G);
+  return blocks_per_cu(kernel, Gm::T * G);
 }
 
 template <class Gm, int G, bool TWREG, bool PF, int WPE = 1, int PWPE = 0>
@@ -609,8 +610,13 @@ static constexpr OlsVariant make_variant(const char *name) {
   v.G = G;
   v.nbuf = Gm::NBUF;
   v.precision = 0;
-  v.pair = PWPE > 0;
+  v.pair = v.detect_pair = PWPE > 0;
   v.unit_cost = 3.0f;
+  v.model = Gm::L <= 256    ? UnitModel{4.1, 0.47, 0.18, 0.11, 1.155}
+            : Gm::L <= 512  ? UnitModel{9.0, 0.61, 0.29, 0.29, 0.993}
+            : Gm::L <= 1024 ? UnitModel{5.9, 0.73, 0.53, 0.73, 1.092}
+            : Gm::L <= 4096 ? UnitModel{5.2, 0.66, 0.47, 0.86, 1.031}
+                            : UnitModel{3.0, 0.40, 0.35, 0.81, 1.0};
   v.lay.L = Gm::L;
   v.lay.T = Gm::T;
   v.lay.E = Gm::E;

@@ -1144,15 +1144,15 @@ static int mixed_batch_blocks_per_cu(int) {
 }
 
 template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
-static int mixed_grid_blocks_per_cu(int) {
+static int mixed_grid_blocks_per_cu(int, int detect) {
+  const void *kernel =
+      detect ? reinterpret_cast<const void *>(
+                   &ols_mixed4096_kernel<H, PF, NT, NW, OCC, SPLIT, true, false>)
+             : reinterpret_cast<const void *>(
+                   &ols_mixed4096_kernel<H, PF, NT, NW, OCC, SPLIT, false, PF == 5>);
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb,
-          reinterpret_cast<const void *>(
-              &ols_mixed4096_kernel<H, PF, NT, NW, OCC, SPLIT, false, PF == 5>),
-          64 * NW, 0) != hipSuccess)
-    return 0;
-  return nb;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 64 * NW, 0) == hipSuccess ? nb
+                                                                                             : 0;
 }
 
 template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
@@ -1169,6 +1169,7 @@ static OlsVariant make_mixed(const char *name, int precision) {
   // The forward FFT costs several templates' worth of time here.
   v.zpb_target = 72;
   v.unit_cost = SPLIT ? 5.0f : 8.0f;
+  v.model = {8.6, 0.39, 0.21, 0.87, 1.044};
   v.lay.L = 4096;
   v.lay.T = 256;
   v.lay.E = 16;

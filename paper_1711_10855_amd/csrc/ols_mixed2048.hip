@@ -591,13 +591,13 @@ static int batch_blocks_per_cu(int) {
 }
 
 template <class H, bool NT, int OCC>
-static int grid_blocks_per_cu(int) {
+static int grid_blocks_per_cu(int, int detect) {
+  const void *kernel =
+      detect ? reinterpret_cast<const void *>(&ols_mixed2048_kernel<H, NT, OCC, true>)
+             : reinterpret_cast<const void *>(&ols_mixed2048_kernel<H, NT, OCC, false>);
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, reinterpret_cast<const void *>(&ols_mixed2048_kernel<H, NT, OCC, false>), 64 * NW,
-          0) != hipSuccess)
-    return 0;
-  return nb;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 64 * NW, 0) == hipSuccess ? nb
+                                                                                             : 0;
 }
 
 template <class H, bool NT, int OCC>
@@ -612,6 +612,7 @@ static OlsVariant make(const char *name, int precision) {
   v.split = 0;
   v.zpb_target = 72;
   v.unit_cost = 8.0f;
+  v.model = {6.0, 0.64, 0.0, 0.59, 1.0};
   v.lay.L = L;
   v.lay.T = 128;
   v.lay.E = 16;

@@ -7,6 +7,7 @@
 
 #include "cand_place.hpp"
 #include "fft_radix.hpp"
+#include "launch_units.hpp"
 #include "layout.hpp"
 
 namespace fdas {
@@ -151,11 +152,11 @@ __host__ __device__ inline int unit_rows(int rows, bool pair) {
 // others, of per2; row-group major inside each part.
 struct UnitGrid {
   int nsb, rows, n1, per1, per2;
+  unsigned b1;  // units of the first part
   __host__ long blocks() const {
-    return (long)n1 * ((rows + per1 - 1) / per1) + (long)(nsb - n1) * ((rows + per2 - 1) / per2);
+    return (long)b1 + (long)(nsb - n1) * ((rows + per2 - 1) / per2);
   }
   __device__ __forceinline__ void unit(unsigned b, int *sb, int *z0, int *z1) const {
-    const unsigned b1 = (unsigned)n1 * (unsigned)((rows + per1 - 1) / per1);
     const bool second = b >= b1;
     const unsigned i = second ? b - b1 : b, n = second ? nsb - n1 : n1;
     const int per = second ? per2 : per1;
@@ -166,8 +167,10 @@ struct UnitGrid {
 };
 // (G: segments per group)
 inline UnitGrid unit_grid(const OlsArgs &a, int G, bool pair) {
-  return {(a.nseg + G - 1) / G, unit_rows(a.nz, pair), a.n1, unit_rows(a.zpb1, pair),
-          unit_rows(a.zpb2, pair)};
+  UnitGrid u{(a.nseg + G - 1) / G, unit_rows(a.nz, pair), a.n1, unit_rows(a.zpb1, pair),
+             unit_rows(a.zpb2, pair), 0u};
+  u.b1 = (unsigned)a.n1 * (unsigned)((u.rows + u.per1 - 1) / u.per1);
+  return u;
 }
 
 // One series of a batch as the persistent kernel sees it.
@@ -203,15 +206,18 @@ struct OlsVariant {
   int precision;     // FDAS_FP32 (0), FDAS_MIXED_FP16 (1), FDAS_MIXED_BF16 (2)
   int split;         // 1: hi + lo split products (FDAS_FLAG_SPLIT)
   int pair;          // 1: has a pair form, used where the bank's rows mirror
+  int detect_pair;   // 1: so has its detection form
   int zpb_target;    // templates per unit where the size of the GPU is not known:
                      // units of that many, or (0) near-equal ones of at most 40
   float unit_cost;   // what a unit's forward transform takes, in templates
+  UnitModel model;   // of the time of a single-spectrum launch
   LayoutDesc lay;
   int lds_bytes;
   hipError_t (*launch)(const OlsArgs &, hipStream_t);
   hipError_t (*launch_batch)(const BatchArgs &, hipStream_t);
   int (*batch_blocks_per_cu)(int pair);
-  int (*grid_blocks_per_cu)(int pair);  // occupancy of the single-spectrum kernel
+  // occupancy of the single-spectrum kernel; detect: of its detection form
+  int (*grid_blocks_per_cu)(int pair, int detect);
 };
 
 const OlsVariant *fp32_variants(int *count);

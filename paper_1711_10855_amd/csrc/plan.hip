@@ -12,6 +12,7 @@
 #include <string>
 #include <vector>
 
+#include "launch_units.hpp"
 #include "noalloc.hpp"
 #include "peaks.hpp"
 #include "plan.hpp"
@@ -40,8 +41,8 @@ struct fdas_plan_s {
   hipStream_t cap_stream = nullptr;
   int cus = 0;
   bool zpb_forced = false;  // FDAS_ZPB or the autotuner fixed it
-  int slots = 0;            // concurrently resident blocks of the grid kernel
-  int pair = 0;             // launches take rows z and -z together
+  int slots[2][2] = {};     // [pair form][detection form] resident blocks of the grid kernel
+  int pair = 0;             // launches may take rows z and -z together
   int last_zpb = 0;         // templates per unit of the last launch (a batch: its largest)
 };
 
@@ -481,76 +482,28 @@ static int plan_cus(fdas_plan_t pl) {
   return pl->cus;
 }
 
-// Blocks of the plan's kernel that the GPU holds at once (0 if unknown).
-static int plan_slots(fdas_plan_t pl) {
-  if (!pl->slots) {
-    const int per = pl->var->grid_blocks_per_cu ? pl->var->grid_blocks_per_cu(pl->pair) : 0;
-    if (per > 0) pl->slots = plan_cus(pl) * per;
+// Blocks of a form of the plan's kernel that the GPU holds at once (0 if unknown).
+// (The detection forms hold fewer where their list of candidates or their
+// registers say so: 7 blocks in place of 8 on a compute unit at 1024 points, 12
+// in place of 16 at 256. Laid out for the plane's, 1800000 bins x 101 rows at 1024
+// points took 284 us.)
+static int plan_slots(fdas_plan_t pl, int pair, int detect) {
+  int &slots = pl->slots[pair][detect];
+  if (!slots) {
+    const int per = pl->var->grid_blocks_per_cu ? pl->var->grid_blocks_per_cu(pair, detect) : 0;
+    if (per > 0) slots = plan_cus(pl) * per;
   }
-  return pl->slots;
+  return slots;
 }
 
-// Templates per work unit of a launch over nsb segment groups. The blocks run
-// in rounds of `slots`, a round as long as its longest unit (its templates
-// and unit_cost for the forward transform). Segment groups that fill whole
-// rounds take all rows in one unit, which pays the forward transform once;
-// those that are left over are split finely enough to fill one more round or
-// a few short ones. (2^20 bins x 101 rows in split BF16: 274 segments on 256
-// slots. As units of 72 and 29 rows, short ones last, 18 long units started
-// when the rest had done theirs: 195 us, against 173 with 256 whole units and
-// the other 18 segments in units of 8. 2^21 x 101 in FP32: 294 against 276 us.
-// 65536 bins in FP16, 18 segments on 512 slots: 61 against 16 us.)
-// A last round with fewer blocks on a compute unit than it holds ends sooner, in
-// proportion down to kAlone of a full one, where a block no longer shares its
-// SIMDs. (Alone against in full company, in units of like size: 1 : 1.5 at 4096
-// points in FP32, 1.64 at 2048, 2.1 at 1024, 1.6 in FP16. 19 segments of 4096
-// points and 33 rows: 323 units of 2 rows 17.6 us, 209 of 3 14.5. Not so after
-// whole rounds, whose blocks end one by one: 2^21 x 101 in FP32 283 us without
-// and 285 with it.)
-constexpr double kAlone = 0.65;
-struct UnitSplit {
-  int64_t n1;
-  int zpb1, zpb2;
-};
-static UnitSplit launch_split(fdas_plan_t pl, int64_t nsb) {
-  const int slots = pl->zpb_forced ? 0 : plan_slots(pl);
-  if (slots <= 0) return {0, pl->zpb, pl->zpb};
-  const int each = pl->pair ? 2 : 1, n = unit_rows(pl->nz, pl->pair);
-  const double fwd = pl->var->unit_cost;
-  UnitSplit best{0, pl->nz, pl->nz};
-  double best_cost = 0.0;
-  const int64_t full = nsb / slots;
-  for (int64_t k = full; k >= 0 && k >= full - 1; --k) {
-    const int64_t rest = nsb - k * slots;
-    for (int g = 1; g <= n; ++g) {
-      const int per = (n + g - 1) / g;
-      if (g > 1 && per == (n + g - 2) / (g - 1)) continue;  // the same units as before
-      const int64_t units = rest * ((n + per - 1) / per), left = units % slots;
-      double last = left ? 1.0 : 0.0;
-      if (left && k == 0)
-        last = std::max(kAlone, (double)((left + pl->cus - 1) / pl->cus) * pl->cus / slots);
-      const double rounds = (double)(units / slots) + last;
-      const double cost = (double)k * (each * n + fwd) + rounds * ((double)each * per + fwd);
-      if (best_cost == 0.0 || cost < best_cost * 0.999) {
-        best_cost = cost;
-        best = {k * slots, pl->nz, std::min(each * per, pl->nz)};
-      }
-      if (rest == 0) break;
-    }
-  }
-  return best;
-}
-
-// Whether a launch over nsb segment groups takes rows z and -z apart, one row
-// to a block: where that leaves a SIMD at most one wavefront (or a compute unit
-// one block of more than four) the time is that of one block, whose second
-// inverse transform is then its longest part. (FP32, 2048 points, 510 rows of
-// segments: 8.1 us against 9.3 as 255 pairs; 765: 9.8 both; 1010: 11.9 against
-// 9.9. FP16: 255 9.1 against 9.3, 303 13.0 against 9.5.)
-static bool rows_apart(fdas_plan_t pl, int64_t nsb) {
-  if (!pl->pair || pl->zpb_forced || plan_cus(pl) <= 0) return false;
-  const int waves = pl->var->T * pl->var->G / 64;
-  return nsb * pl->nz <= (int64_t)pl->cus * std::max(1, 4 / std::max(1, waves));
+// Work units of a launch over nsb segment groups: FDAS_ZPB and the autotuner fix
+// one size; else the layout of least estimated time.
+static UnitSplit launch_split(fdas_plan_t pl, int64_t nsb, int detect) {
+  const int pair = pl->pair && (!detect || pl->var->detect_pair);
+  if (pl->zpb_forced || plan_cus(pl) <= 0) return {0, pl->zpb, pl->zpb, pair};
+  const int slots1 = plan_slots(pl, 0, detect), slots2 = pair ? plan_slots(pl, 1, detect) : 0;
+  if (slots1 <= 0 || (pair && slots2 <= 0)) return {0, pl->zpb, pl->zpb, pair};
+  return pick_units(pl->var->model, nsb, pl->nz, pl->cus, slots2, slots1);
 }
 
 static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *power, int64_t ld,
@@ -558,8 +511,7 @@ static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *p
   const int64_t nseg = (nbins + pl->U - 1) / pl->U;
   if (nseg > INT_MAX / 2) return set_error(FDAS_ERR_UNSUPPORTED, "nbins %lld too large", (long long)nbins);
   const int64_t nsb = (nseg + pl->var->G - 1) / pl->var->G;
-  const bool apart = rows_apart(pl, nsb);
-  const UnitSplit split = apart ? UnitSplit{0, 1, 1} : launch_split(pl, nsb);
+  const UnitSplit split = launch_split(pl, nsb, cand.count != nullptr);
   pl->last_zpb = split.n1 ? split.zpb1 : split.zpb2;
   const int64_t nzg = (pl->nz + split.zpb2 - 1) / split.zpb2;
   if (nsb * nzg > (int64_t)UINT_MAX)
@@ -582,7 +534,7 @@ static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *p
   while ((1 << a.bank_log2) < pl->L) ++a.bank_log2;
   a.consts = pl->consts;
   a.cand = cand;
-  a.pair = apart ? 0 : pl->pair;
+  a.pair = split.pair;
   hipError_t e = pl->var->launch(a, s);
   if (e != hipSuccess) return hip_error(e, "correlation kernel launch");
   return FDAS_OK;
@@ -633,6 +585,10 @@ static int series_desc(fdas_plan_t pl, const fdas_series &x, int i, SeriesDesc *
   *cost = (double)d->nz * (double)x.nbins;
   return FDAS_OK;
 }
+
+// (Where a batch of less than a round is laid out: the time of a block that does
+// not share its SIMDs, against that of one in full company.)
+constexpr double kAlone = 0.65;
 
 // Work items of a batch, its series in the order in which blocks take them
 // (largest first): one item per (series, segment) with all rows, which pays the
