@@ -1,9 +1,10 @@
-// How a single-spectrum launch is cut into work units. Plain C++: the choice
-// also runs on the host.
+// How launches are cut into work units: of a single spectrum, and the items of a
+// batch. Plain C++: the choices also run on the host.
 #pragma once
 
 #include <algorithm>
 #include <cstdint>
+#include <utility>
 
 namespace fdas {
 
@@ -117,6 +118,93 @@ inline UnitSplit pick_units(const UnitModel &m, int64_t nsb, int nz, int cus, in
         per = (n + next - 1) / next;
       }
       if (k == 0) break;
+    }
+  }
+  return best;
+}
+
+// What the time of a batch depends on, in templates of one row: what an item
+// takes beside its rows (its forward transform, and the wait for the next item,
+// which counts most where a block is one wave), the share of an item for the
+// uneven end, and a block's time alone as a share of that in full company.
+struct BatchModel {
+  double item, end, alone;
+};
+
+// Work items of a batch, its series in the order in which blocks take them
+// (largest first): one item per (series, segment group) with all rows, which pays
+// the forward transform once, but for the series from `tail` on, which make up
+// the last round of the GPU's block slots: those in near-equal groups of at most
+// `zpb` rows, so that the blocks end together. The size is the one whose work,
+// spread over the slots, and the share of an item for the end are least; a batch
+// of less than a round is all tail, and its blocks run in rounds as those of a
+// single spectrum do. The constants of the FP32 kernels are fitted to 16 batches in
+// up to 60 layouts each; what this picks takes on average 1.01 times the fastest
+// of them at 256, 512 and 4096 points, 1.02 at 2048, 1.03 at 1024 and in 16
+// bits. (5 series of 20
+// segments and 201 rows in FP32 on 512 slots: items of 34 rows, 0.82 rounds, 110
+// us; of 26, 1.09, 137; of 14, 2.05, 112. 12 series of 2^19 .. 2^21 bins and 33
+// .. 101 rows in FP32: 1302 us in groups of at most 40 rows, 1257 this way; 6
+// series of 95000 .. 190000 bins in FP16: 116 against 86 us. With one price of 3
+// rows for every FP32 item, 3 series of 220 segments and 26 rows at 512 points
+// went in items of 4: 50 us, 30 in items of 14.)
+struct BatchUnits {
+  int tail, zpb;
+};
+
+// get(k): segment groups and rows of the series at place k of n. The tail is
+// summed by its numbers of rows, of which there are few (beyond kKinds the
+// others count as the last), so that the many sizes tried cost little however
+// many series there are: 2000 one-segment series took 60 us of host time.
+template <class Get>
+inline BatchUnits pick_batch(const BatchModel &m, int64_t slots, int cus, bool pair, int n, Get &&get) {
+  constexpr int kKinds = 64;
+  int rows = 0;
+  for (int k = 0; k < n; ++k) rows = std::max(rows, get(k).second);
+  struct {
+    int rows;
+    int64_t groups;
+  } kind[kKinds];
+  int kinds = 0, tail = n, tail_rows = 1;
+  double work = 0.0, head = 0.0;
+  while (tail > 0 && work < (double)slots * (rows + m.item)) {
+    const std::pair<int64_t, int> x = get(--tail);
+    work += (double)x.first * (x.second + m.item);
+    tail_rows = std::max(tail_rows, x.second);
+    int i = 0;
+    while (i < kinds && kind[i].rows != x.second) ++i;
+    if (i == kKinds) i = kKinds - 1;
+    if (i == kinds) kind[kinds++] = {x.second, 0};
+    kind[i].groups += x.first;
+  }
+  for (int k = 0; k < tail; ++k) {
+    const std::pair<int64_t, int> x = get(k);
+    head += (double)x.first * (x.second + m.item);
+  }
+  BatchUnits best{tail, tail_rows};
+  double best_time = -1.0;
+  for (int groups : {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32}) {
+    int zpb = (tail_rows + groups - 1) / groups;
+    if (pair) zpb += zpb & 1;
+    work = head;
+    int64_t units = 0;
+    int longest = 0;
+    for (int i = 0; i < kinds; ++i) {
+      const int ng = (kind[i].rows + zpb - 1) / zpb;
+      work += (double)kind[i].groups * (kind[i].rows + m.item * ng);
+      units += kind[i].groups * ng;
+      longest = std::max(longest, (kind[i].rows + ng - 1) / ng);
+    }
+    double time = std::max(zpb + m.item, work / (double)slots + m.end * (zpb + m.item));
+    if (tail == 0) {
+      const int64_t left = units % slots;
+      const double share = (double)((left + cus - 1) / cus * cus) / (double)slots;
+      time = (longest + m.item) *
+             ((double)(units / slots) + (left ? std::max(m.alone, share) : 0.0));
+    }
+    if (best_time < 0.0 || time < best_time * 0.999) {
+      best_time = time;
+      best.zpb = zpb;
     }
   }
   return best;

@@ -1132,15 +1132,15 @@ static hipError_t launch_mixed4096_batch(const BatchArgs &a, hipStream_t st) {
 // (the pair form has the occupancy of the single one: the same registers and LDS)
 template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
 static int mixed_batch_blocks_per_cu(int) {
-  if (!mixed_batch_persistent()) return 1;  // flat launch: the grid is the item count
+  const void *kernel =
+      mixed_batch_persistent()
+          ? reinterpret_cast<const void *>(
+                &ols_mixed4096_persistent_kernel<H, PF, NT, NW, OCC, SPLIT, PF == 5>)
+          : reinterpret_cast<const void *>(
+                &ols_mixed4096_items_kernel<H, PF, NT, NW, OCC, SPLIT, PF == 5>);
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb,
-          reinterpret_cast<const void *>(
-              &ols_mixed4096_persistent_kernel<H, PF, NT, NW, OCC, SPLIT, PF == 5>),
-          64 * NW, 0) != hipSuccess)
-    return 1;
-  return nb;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 64 * NW, 0) == hipSuccess ? nb
+                                                                                             : 1;
 }
 
 template <class H, int PF, bool NT, int NW, int OCC, bool SPLIT>
@@ -1168,8 +1168,8 @@ static OlsVariant make_mixed(const char *name, int precision) {
   v.pair = PF == 5;
   // The forward FFT costs several templates' worth of time here.
   v.zpb_target = 72;
-  v.unit_cost = SPLIT ? 5.0f : 8.0f;
   v.model = {8.6, 0.39, 0.21, 0.87, 1.044};
+  v.batch_model = SPLIT ? BatchModel{5.0, 0.5, 0.65} : BatchModel{8.0, 0.5, 0.65};
   v.lay.L = 4096;
   v.lay.T = 256;
   v.lay.E = 16;

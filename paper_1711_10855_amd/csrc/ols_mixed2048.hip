@@ -581,13 +581,12 @@ static hipError_t launch_batch(const BatchArgs &a, hipStream_t st) {
 
 template <class H, bool NT, int OCC>
 static int batch_blocks_per_cu(int) {
-  if (!batch_persistent()) return 1;
+  const void *kernel =
+      batch_persistent() ? reinterpret_cast<const void *>(&ols_mixed2048_persistent_kernel<H, NT, OCC>)
+                         : reinterpret_cast<const void *>(&ols_mixed2048_items_kernel<H, NT, OCC>);
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, reinterpret_cast<const void *>(&ols_mixed2048_persistent_kernel<H, NT, OCC>),
-          64 * NW, 0) != hipSuccess)
-    return 1;
-  return nb;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 64 * NW, 0) == hipSuccess ? nb
+                                                                                             : 1;
 }
 
 template <class H, bool NT, int OCC>
@@ -611,8 +610,8 @@ static OlsVariant make(const char *name, int precision) {
   v.precision = precision;
   v.split = 0;
   v.zpb_target = 72;
-  v.unit_cost = 8.0f;
   v.model = {6.0, 0.64, 0.0, 0.59, 1.0};
+  v.batch_model = {8.0, 0.5, 0.65};
   v.lay.L = L;
   v.lay.T = 128;
   v.lay.E = 16;

@@ -209,13 +209,13 @@ struct OlsVariant {
   int detect_pair;   // 1: so has its detection form
   int zpb_target;    // templates per unit where the size of the GPU is not known:
                      // units of that many, or (0) near-equal ones of at most 40
-  float unit_cost;   // what a unit's forward transform takes, in templates
   UnitModel model;   // of the time of a single-spectrum launch
+  BatchModel batch_model;  // and of a batch
   LayoutDesc lay;
   int lds_bytes;
   hipError_t (*launch)(const OlsArgs &, hipStream_t);
   hipError_t (*launch_batch)(const BatchArgs &, hipStream_t);
-  int (*batch_blocks_per_cu)(int pair);
+  int (*batch_blocks_per_cu)(int pair);  // of the batch kernel that runs
   // occupancy of the single-spectrum kernel; detect: of its detection form
   int (*grid_blocks_per_cu)(int pair, int detect);
 };

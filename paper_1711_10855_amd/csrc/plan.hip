@@ -486,7 +486,7 @@ static int plan_cus(fdas_plan_t pl) {
 // (The detection forms hold fewer where their list of candidates or their
 // registers say so: 7 blocks in place of 8 on a compute unit at 1024 points, 12
 // in place of 16 at 256. Laid out for the plane's, 1800000 bins x 101 rows at 1024
-// points took 284 us.)
+// points took 284 us, and 191 laid out for its own.)
 static int plan_slots(fdas_plan_t pl, int pair, int detect) {
   int &slots = pl->slots[pair][detect];
   if (!slots) {
@@ -586,70 +586,13 @@ static int series_desc(fdas_plan_t pl, const fdas_series &x, int i, SeriesDesc *
   return FDAS_OK;
 }
 
-// (Where a batch of less than a round is laid out: the time of a block that does
-// not share its SIMDs, against that of one in full company.)
-constexpr double kAlone = 0.65;
-
-// Work items of a batch, its series in the order in which blocks take them
-// (largest first): one item per (series, segment) with all rows, which pays the
-// forward transform once, but for the series from `tail` on, which make up the
-// last round of the GPU's block slots: those in near-equal groups of at most
-// `zpb` templates, so that the blocks end together. The size is the one whose
-// work, spread over the slots, and half an item for the uneven end are least;
-// a batch of less than a round is all tail, and its blocks run in rounds as
-// those of a single spectrum do. (5 series of 20 segments and 201 rows in FP32
-// on 512 slots: items of 34 rows, 0.82 rounds, 110 us; of 26, 1.09, 137; of 14,
-// 2.05, 112. 12 series of 2^19 .. 2^21 bins and
-// 33 .. 101 rows in FP32: 1302 us in groups of at most 40 rows, 1257 this way; 6
-// series of 95000 .. 190000 bins in FP16: 116 against 86 us.) FDAS_ZPB or the
-// autotuner fixes one size for all. get(k): segment groups and rows of the
-// series at place k.
-struct BatchUnits {
-  int tail, zpb;
-};
+// Items of a batch whose series at place k has get(k) = (segment groups, rows).
+// FDAS_ZPB and the autotuner fix one size for all.
 template <class Get>
 static BatchUnits batch_units(fdas_plan_t pl, int n, Get &&get) {
   if (pl->zpb_forced || plan_cus(pl) <= 0) return {0, pl->zpb};
-  const double slots = (double)pl->cus * std::max(1, pl->var->batch_blocks_per_cu(pl->pair));
-  const double fwd = pl->var->unit_cost;
-  int rows = 0;
-  for (int k = 0; k < n; ++k) rows = std::max(rows, get(k).second);
-  int tail = n, tail_rows = 1;
-  double work = 0.0;
-  while (tail > 0 && work < slots * (rows + fwd)) {
-    const auto x = get(--tail);
-    work += (double)x.first * (x.second + fwd);
-    tail_rows = std::max(tail_rows, x.second);
-  }
-  double head = 0.0;
-  for (int k = 0; k < tail; ++k) head += (double)get(k).first * (get(k).second + fwd);
-  BatchUnits best{tail, tail_rows};
-  double best_time = 0.0;
-  for (int groups : {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32}) {
-    int zpb = (tail_rows + groups - 1) / groups;
-    if (pl->pair) zpb += zpb & 1;
-    work = head;
-    int64_t units = 0;
-    int longest = 0;
-    for (int k = tail; k < n; ++k) {
-      const auto x = get(k);
-      const int ng = (x.second + zpb - 1) / zpb;
-      work += (double)x.first * (x.second + fwd * ng);
-      units += x.first * ng;
-      longest = std::max(longest, (x.second + ng - 1) / ng);
-    }
-    double time = std::max(zpb + fwd, work / slots + 0.5 * (zpb + fwd));
-    if (tail == 0) {
-      const double full = std::floor(units / slots), left = units - full * slots;
-      time = (longest + fwd) *
-             (full + (left > 0.0 ? std::max(kAlone, std::ceil(left / pl->cus) * pl->cus / slots) : 0.0));
-    }
-    if (best_time == 0.0 || time < best_time * 0.999) {
-      best_time = time;
-      best.zpb = zpb;
-    }
-  }
-  return best;
+  const int64_t slots = (int64_t)pl->cus * std::max(1, pl->var->batch_blocks_per_cu(pl->pair));
+  return pick_batch(pl->var->batch_model, slots, pl->cus, pl->pair, n, get);
 }
 
 // Sets a series' templates per item: near-equal groups of at most zpb.
@@ -728,7 +671,7 @@ int plan_convolve_batch(fdas_plan_t pl, const fdas_series *series, int nseries, 
   std::vector<SeriesDesc> sorted(nseries);
   for (int k = 0; k < nseries; ++k) sorted[k] = desc[order[k]];
   const BatchUnits units = batch_units(pl, nseries, [&](int k) {
-    return std::make_pair((int64_t)(sorted[k].nseg + G - 1) / G, sorted[k].nz);
+    return std::make_pair((int64_t)((sorted[k].nseg + G - 1) / G), sorted[k].nz);
   });
   int64_t total = 0;
   int most = 0;  // templates per unit of the largest unit, for plan info
@@ -835,21 +778,20 @@ int plan_convolve_batch_noalloc(fdas_plan_t pl, const fdas_series *series, int n
                      nseries, kNoAllocMaxSeries);
   const int G = pl->var->G;
   double cost[kNoAllocMaxSeries];
-  int order[kNoAllocMaxSeries];
+  int order[kNoAllocMaxSeries], rows[kNoAllocMaxSeries], groups[kNoAllocMaxSeries];
   for (int i = 0; i < nseries; ++i) {
     SeriesDesc d;
     const int st = series_desc(pl, series[i], i, &d, &cost[i]);
     if (st != FDAS_OK) return st;
     order[i] = i;
+    rows[i] = d.nz;
+    groups[i] = (d.nseg + G - 1) / G;
   }
   // largest first, ties in input order (the order the graph path uses)
   std::sort(order, order + nseries,
             [&](int a, int b) { return cost[a] > cost[b] || (cost[a] == cost[b] && a < b); });
   const BatchUnits units = batch_units(pl, nseries, [&](int k) {
-    SeriesDesc d;
-    double c = 0.0;
-    (void)series_desc(pl, series[order[k]], order[k], &d, &c);
-    return std::make_pair((int64_t)(d.nseg + G - 1) / G, d.nz);
+    return std::make_pair((int64_t)groups[order[k]], rows[order[k]]);
   });
   void *base = nullptr;
   int st = noalloc_scratch(pl->device, &base);
