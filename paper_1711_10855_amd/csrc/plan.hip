@@ -106,7 +106,9 @@ static int build_plan_with(fdas_plan_t *out, const fdas_params &p, int nz, int d
 // (U = L - m >= L/2 unless the caller fixed L) and a few template-group sizes
 // on a synthetic spectrum, keep the fastest per plane point. Results are
 // cached in a text file (FDAS_TUNE_CACHE, one line per key) keyed by device
-// architecture, CU count, m, nz, precision, split form and segment length.
+// architecture, CU count, m, nz, precision, split form, segment length and
+// half-bin rows (whose plans run the one-row kernels: a size timed for pairs is
+// not theirs).
 struct TuneChoice {
   const OlsVariant *var = nullptr;
   int L = 0, zpb = 0;
@@ -124,8 +126,9 @@ static std::string tune_key(const fdas_params &p, int nz, int device) {
   for (auto &ch : arch)
     if (ch == ' ' || ch == ':') ch = '_';
   char buf[256];
-  std::snprintf(buf, sizeof(buf), "%s cu%d m%d nz%d prec%d split%d L%d", arch.c_str(), cus, p.m,
-                nz, p.precision, (p.flags & FDAS_FLAG_SPLIT) ? 1 : 0, p.seg_len);
+  std::snprintf(buf, sizeof(buf), "%s cu%d m%d nz%d prec%d split%d L%d%s", arch.c_str(), cus, p.m,
+                nz, p.precision, (p.flags & FDAS_FLAG_SPLIT) ? 1 : 0, p.seg_len,
+                (p.flags & FDAS_FLAG_INTERBIN) ? " interbin" : "");
   return buf;
 }
 
