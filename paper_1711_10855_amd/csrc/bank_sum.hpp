@@ -18,15 +18,17 @@
 // all. One sincospi per term and frequency instead took 227 us for 101 rows of
 // 2048 frequencies (257 taps), against 12 us.
 //
-// ROWS is 4 where that makes more blocks than the 256 compute units, and 2
+// ROWS is 4 where that makes more blocks than there are compute units, and 2
 // below, where the chip is not full and the chains of table reads and of taps
 // from memory bound it: half the rows, and twice the taps staged and table reads
-// in flight at a time. (101 rows of 2048: 19.9 us with 4, 11.6 with 2. The whole
-// call for 201 rows of 4096, 513 taps, 231 blocks of 4: 67 against 62 us; of
-// 8192, 455 blocks: 79 against 82.)
+// in flight at a time. (On 256 compute units, 101 rows of 2048: 19.9 us with 4,
+// 11.6 with 2. The whole call for 201 rows of 4096, 513 taps, 231 blocks of 4: 67
+// against 62 us; of 8192, 455 blocks: 79 against 82.)
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <cstdint>
 
 namespace fdas {
 
@@ -119,6 +121,15 @@ __global__ void __launch_bounds__(64 * kBankWaves)
   }
 }
 
+// Compute units of the current device (256 if that cannot be asked).
+static int bank_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 256;
+  return cus;
+}
+
 template <bool HALF, class Put>
 static void launch_bank_part(const void *h, int nzg, int interbin, int m, int L, Put put,
                              hipStream_t s) {
@@ -129,7 +140,7 @@ static void launch_bank_part(const void *h, int nzg, int interbin, int m, int L,
     return dim3(gx, (unsigned)((rows + kBankWaves * per_wave - 1) / (kBankWaves * per_wave)));
   };
   const dim3 wide = blocks(4);
-  if (wide.x * wide.y > 256)
+  if ((int64_t)wide.x * wide.y > bank_cus())
     hipLaunchKernelGGL((bank_sum_kernel<HALF, 4, Put>), wide, dim3(64 * kBankWaves), lds, s,
                        static_cast<const c64b *>(h), nzg, interbin, m, L, put);
   else
