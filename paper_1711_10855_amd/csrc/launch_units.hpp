@@ -16,6 +16,9 @@ struct UnitModel {
   double fixed;    // the share that does not shrink with fewer blocks around it
   double step;     // how far blocks keep step (1: in rounds, 0: as slots fall free)
   double single;   // a row of the single form against one of the pair form
+  // What a template takes longer in a unit of 100 rows or more (and in proportion
+  // in a shorter one) on ragged planes, in the pair and in the single form.
+  double ragged[2];
 };
 
 // Units of a launch: every row of the first n1 segment groups, then zpb2 rows at
@@ -38,10 +41,18 @@ struct UnitSplit {
 // spread over the slots, and a share of one unit for the end. Which one it is
 // differs by kernel: blocks of one wave share a SIMD four ways and drift, a
 // block of 16 waves holds half a compute unit and keeps step.
+//
+// A plane that the caches do not hold, whose rows or segments do not lie on 64
+// bytes, is ragged: where two segments or two stores of one meet in a line, the
+// line is written twice unless both halves come soon after one another, which
+// they do the less the more rows a unit has. (2048 points, m = 250, 2^22 bins x
+// 101 rows: units of 102 rows 758 us, 52 695, 34 671, 18 629; m = 256, aligned: 576,
+// 558, 553, 584.)
+//
 // The constants are fitted to measured times of 5 numbers of rows (17 .. 201) x
-// 9 lengths (15000 .. 2^21 bins) in up to 50 layouts each; what the estimate
-// picks takes on average 1.01 times the fastest of them at 256 and 512 points,
-// 1.004 times at the others. (256 points, 202 rows of single form, 1366 groups
+// 14 lengths (15000 .. 2^23 bins) in up to 50 layouts each; what the estimate
+// picks takes on average 1.01 times the fastest of them at 256 to 1024 points,
+// 1.005 times at the others. (256 points, 202 rows of single form, 1366 groups
 // on 4096 slots: units of 202 rows 203 us, 101 150, 41 140, 21 137, 9 155. 2048
 // points, 101 rows, 140 segments on 1024 slots: units of 102 rows 162 us, 22
 // 46.8, 16 43.0, 14 44.0, 12 52.7, 2 82.6. Units counted in whole rounds alone,
@@ -51,15 +62,19 @@ struct UnitCost {
   UnitModel m;
   int64_t nsb, slots;
   int cus, nz, each;  // each: rows counted by one of n
+  double ragged;      // of UnitModel's for this form, or 0
 
   double operator()(int64_t k, int per) const {
     const int n = (nz + each - 1) / each, groups = (n + per - 1) / per;
     const double rest = (double)(nsb - k * slots), units = rest * groups;
     const double full = (double)(int64_t)(units / (double)slots);
     const double left = units - full * (double)slots;
-    const double all = nz + m.forward;
-    const double unit = rest == 0.0 ? all : std::min(each * per, nz) + m.forward;
-    const double work = rest / (double)slots * (nz + m.forward * groups) + (double)k * all;
+    const int rows = std::min(each * per, nz);
+    const double longer = 1.0 + ragged * std::min(rows, 100) * 0.01;
+    const double all = (nz + m.forward) * (1.0 + ragged * std::min(nz, 100) * 0.01);
+    const double unit = rest == 0.0 ? all : (rows + m.forward) * longer;
+    const double work =
+        rest / (double)slots * (nz + m.forward * groups) * longer + (double)k * all;
     const double spread = std::max(m.alone * unit, m.fixed * unit + (1.0 - m.fixed) * work);
     double last = 0.0;
     if (left > 0.0) {
@@ -86,7 +101,7 @@ struct UnitCost {
 // then finer ones until the forward transforms alone cost more. `looked`, if
 // given, counts them.
 inline UnitSplit pick_units(const UnitModel &m, int64_t nsb, int nz, int cus, int64_t pair_slots,
-                            int64_t single_slots, int64_t *looked = nullptr) {
+                            int64_t single_slots, bool ragged, int64_t *looked = nullptr) {
   UnitSplit best{0, nz, nz, pair_slots > 0};
   double best_cost = -1.0;
   const double few = m.fixed < 1.0 ? std::max(0.0, (m.alone - m.fixed) / (1.0 - m.fixed)) : 0.0;
@@ -94,7 +109,7 @@ inline UnitSplit pick_units(const UnitModel &m, int64_t nsb, int nz, int cus, in
     const int64_t slots = pair ? pair_slots : single_slots;
     if (slots <= 0) continue;
     const double factor = pair_slots > 0 && !pair ? m.single : 1.0;
-    const UnitCost cost{m, nsb, slots, cus, nz, pair ? 2 : 1};
+    const UnitCost cost{m, nsb, slots, cus, nz, pair ? 2 : 1, ragged ? m.ragged[pair ? 0 : 1] : 0.0};
     const int n = (nz + cost.each - 1) / cost.each;
     // (the single form of a plan with pairs: without whole-row units only)
     const int64_t full = pair || pair_slots <= 0 ? nsb / slots : 0;

@@ -611,11 +611,12 @@ static constexpr OlsVariant make_variant(const char *name) {
   v.nbuf = Gm::NBUF;
   v.precision = 0;
   v.pair = v.detect_pair = PWPE > 0;
-  v.model = Gm::L <= 256    ? UnitModel{4.1, 0.47, 0.18, 0.11, 1.155}
-            : Gm::L <= 512  ? UnitModel{9.0, 0.61, 0.29, 0.29, 0.993}
-            : Gm::L <= 1024 ? UnitModel{5.9, 0.73, 0.53, 0.73, 1.092}
-            : Gm::L <= 4096 ? UnitModel{5.2, 0.66, 0.47, 0.86, 1.031}
-                            : UnitModel{3.0, 0.40, 0.35, 0.81, 1.0};
+  v.model = Gm::L <= 256    ? UnitModel{4.1, 0.47, 0.18, 0.11, 1.155, {0.0, 0.0}}
+            : Gm::L <= 512  ? UnitModel{9.0, 0.61, 0.29, 0.29, 0.993, {0.85, 0.91}}
+            : Gm::L <= 1024 ? UnitModel{5.9, 0.73, 0.53, 0.73, 1.092, {0.65, 0.24}}
+            : Gm::L <= 2048 ? UnitModel{5.2, 0.66, 0.47, 0.86, 1.031, {1.11, 0.50}}
+            : Gm::L <= 4096 ? UnitModel{5.2, 0.66, 0.47, 0.86, 1.031, {0.0, 0.0}}
+                            : UnitModel{3.0, 0.40, 0.35, 0.81, 1.0, {0.0, 0.0}};
   v.batch_model = Gm::L <= 512    ? BatchModel{25.8, 0.40, 0.14}
                   : Gm::L <= 1024 ? BatchModel{2.0, 0.82, 0.47}
                                   : BatchModel{4.6, 0.37, 0.82};

@@ -501,12 +501,12 @@ static int plan_slots(fdas_plan_t pl, int pair, int detect) {
 
 // Work units of a launch over nsb segment groups: FDAS_ZPB and the autotuner fix
 // one size; else the layout of least estimated time.
-static UnitSplit launch_split(fdas_plan_t pl, int64_t nsb, int detect) {
+static UnitSplit launch_split(fdas_plan_t pl, int64_t nsb, int detect, bool ragged) {
   const int pair = pl->pair && (!detect || pl->var->detect_pair);
   if (pl->zpb_forced || plan_cus(pl) <= 0) return {0, pl->zpb, pl->zpb, pair};
   const int slots1 = plan_slots(pl, 0, detect), slots2 = pair ? plan_slots(pl, 1, detect) : 0;
   if (slots1 <= 0 || (pair && slots2 <= 0)) return {0, pl->zpb, pl->zpb, pair};
-  return pick_units(pl->var->model, nsb, pl->nz, pl->cus, slots2, slots1);
+  return pick_units(pl->var->model, nsb, pl->nz, pl->cus, slots2, slots1, ragged);
 }
 
 static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *power, int64_t ld,
@@ -514,7 +514,12 @@ static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *p
   const int64_t nseg = (nbins + pl->U - 1) / pl->U;
   if (nseg > INT_MAX / 2) return set_error(FDAS_ERR_UNSUPPORTED, "nbins %lld too large", (long long)nbins);
   const int64_t nsb = (nseg + pl->var->G - 1) / pl->var->G;
-  const UnitSplit split = launch_split(pl, nsb, cand.count != nullptr);
+  // (a plane of 256 MB is what the last cache holds)
+  const bool detect = cand.count != nullptr;
+  const bool lines =
+      ((reinterpret_cast<uintptr_t>(power) | (uintptr_t)(ld * 4) | (uintptr_t)pl->U * 4) & 63) == 0;
+  const bool ragged = !detect && !lines && ld * pl->nz * 4 > ((int64_t)1 << 28);
+  const UnitSplit split = launch_split(pl, nsb, detect, ragged);
   pl->last_zpb = split.n1 ? split.zpb1 : split.zpb2;
   const int64_t nzg = (pl->nz + split.zpb2 - 1) / split.zpb2;
   if (nsb * nzg > (int64_t)UINT_MAX)

@@ -15,14 +15,15 @@ PROGRAM = r"""
 #include "launch_units.hpp"
 using namespace fdas;
 int main(int argc, char **argv) {
-  const UnitModel m{std::atof(argv[1]), std::atof(argv[2]), std::atof(argv[3]), std::atof(argv[4]), 1.1};
+  const UnitModel m{std::atof(argv[1]), std::atof(argv[2]), std::atof(argv[3]), std::atof(argv[4]), 1.1,
+                    {0.9, 0.4}};
   const int cus = std::atoi(argv[5]), nz = std::atoi(argv[8]);
   const long pair_slots = std::atol(argv[6]), single_slots = std::atol(argv[7]);
-  const bool all = std::atoi(argv[9]);
+  const bool all = std::atoi(argv[9]), ragged = std::atoi(argv[10]);
   long worst = 0;
   for (long nsb = 1; nsb < 100000; nsb += 1 + nsb / 7) {
     int64_t looked = 0;
-    const UnitSplit s = pick_units(m, nsb, nz, cus, pair_slots, single_slots, &looked);
+    const UnitSplit s = pick_units(m, nsb, nz, cus, pair_slots, single_slots, ragged, &looked);
     if (looked > worst) worst = looked;
     const long slots = s.pair ? pair_slots : single_slots;
     if (s.n1 < 0 || s.n1 > nsb || s.n1 % slots || s.zpb1 != nz || s.zpb2 < 1 || s.zpb2 > nz ||
@@ -32,7 +33,7 @@ int main(int argc, char **argv) {
     double best = -1.0;
     for (int pair = pair_slots > 0; pair >= 0; --pair) {
       const long sl = pair ? pair_slots : single_slots;
-      const UnitCost cost{m, nsb, sl, cus, nz, pair ? 2 : 1};
+      const UnitCost cost{m, nsb, sl, cus, nz, pair ? 2 : 1, ragged ? m.ragged[pair ? 0 : 1] : 0.0};
       const int n = pair ? (nz + 1) / 2 : nz;
       const long full = pair || pair_slots <= 0 ? nsb / sl : 0;
       for (long k : {0l, full - 1, full})
@@ -41,7 +42,7 @@ int main(int argc, char **argv) {
           if (best < 0.0 || c < best) best = c;
         }
     }
-    const UnitCost cost{m, nsb, slots, cus, nz, s.pair ? 2 : 1};
+    const UnitCost cost{m, nsb, slots, cus, nz, s.pair ? 2 : 1, ragged ? m.ragged[s.pair ? 0 : 1] : 0.0};
     const double c = cost(s.n1 / slots, s.pair ? (s.zpb2 + 1) / 2 : s.zpb2) *
                      (pair_slots > 0 && !s.pair ? m.single : 1.0);
     if (c > best * 1.0021) return std::printf("nsb %ld: %g, least %g\n", nsb, c, best), 1;
@@ -63,9 +64,9 @@ def program(tmp_path_factory):
     return str(exe)
 
 
-def run(program, model, cus, pair_slots, single_slots, nz, everything):
+def run(program, model, cus, pair_slots, single_slots, nz, everything, ragged):
     res = subprocess.run([program, *map(str, model), str(cus), str(pair_slots), str(single_slots),
-                          str(nz), str(int(everything))], capture_output=True, text=True)
+                          str(nz), str(int(everything)), str(ragged)], capture_output=True, text=True)
     assert res.returncode == 0, res.stdout
     return int(res.stdout)
 
@@ -75,15 +76,18 @@ def run(program, model, cus, pair_slots, single_slots, nz, everything):
                          [(256, 1024, 1024), (256, 3072, 4096), (256, 0, 512), (256, 256, 256),
                           (32, 0, 64), (1, 1, 1), (304, 1824, 2432)])
 @pytest.mark.parametrize("nz", [1, 2, 3, 17, 101, 402])
-def test_the_pick_is_the_cheapest_layout(program, model, cus, pair_slots, single_slots, nz):
+@pytest.mark.parametrize("ragged", [0, 1])
+def test_the_pick_is_the_cheapest_layout(program, model, cus, pair_slots, single_slots, nz, ragged):
     # (layouts within 0.1% of one looked at earlier are passed over, twice at most)
-    run(program, model, cus, pair_slots, single_slots, nz, True)
+    run(program, model, cus, pair_slots, single_slots, nz, True, ragged)
 
 
 @pytest.mark.parametrize("model", MODELS)
 @pytest.mark.parametrize("pair_slots,single_slots", [(1024, 1024), (3072, 4096), (0, 512)])
 def test_few_layouts_are_looked_at(program, model, pair_slots, single_slots):
     """Every call makes this choice: some 1e-8 s for each layout it looks at. One
-    by one, 20001 rows are up to 40000 of them."""
-    assert run(program, model, 256, pair_slots, single_slots, 201, False) <= 120
-    assert run(program, model, 256, pair_slots, single_slots, 20001, False) <= 700
+    by one, 20001 rows are up to 40000 of them; their pairs come in 2 sqrt(10001)
+    sizes, with three numbers of whole-row rounds, and the rows in 2 sqrt(20001)."""
+    for ragged in (0, 1):
+        assert run(program, model, 256, pair_slots, single_slots, 201, False, ragged) <= 120
+        assert run(program, model, 256, pair_slots, single_slots, 20001, False, ragged) <= 900
