@@ -144,6 +144,8 @@ inline UnitSplit pick_units(const UnitModel &m, int64_t nsb, int nz, int cus, in
 // uneven end, and a block's time alone as a share of that in full company.
 struct BatchModel {
   double item, end, alone;
+  // As in UnitModel, for planes ragged in their rows and in their segments.
+  double ragged_rows, ragged_segments;
 };
 
 // Work items of a batch, its series in the order in which blocks take them
@@ -167,12 +169,19 @@ struct BatchUnits {
   int tail, zpb;
 };
 
+// Ragged planes (`ragged`: the model's, else 0) are all tail: their items are short
+// for the same reason as the units above. (4 series of 2^20 bins x 101 rows at 2048
+// points, m = 250: 655 us whole, 634 this way. At 512 points 2 series of 3000001
+// bins and odd rows: 802, 745. Odd rows at 2048 points with m = 256 are no slower
+// whole.)
+//
 // get(k): segment groups and rows of the series at place k of n. The tail is
 // summed by its numbers of rows, of which there are few (beyond kKinds the
 // others count as the last), so that the many sizes tried cost little however
 // many series there are: 2000 one-segment series took 60 us of host time.
 template <class Get>
-inline BatchUnits pick_batch(const BatchModel &m, int64_t slots, int cus, bool pair, int n, Get &&get) {
+inline BatchUnits pick_batch(const BatchModel &m, int64_t slots, int cus, bool pair, double ragged,
+                             int n, Get &&get) {
   constexpr int kKinds = 64;
   int rows = 0;
   for (int k = 0; k < n; ++k) rows = std::max(rows, get(k).second);
@@ -182,7 +191,7 @@ inline BatchUnits pick_batch(const BatchModel &m, int64_t slots, int cus, bool p
   } kind[kKinds];
   int kinds = 0, tail = n, tail_rows = 1;
   double work = 0.0, head = 0.0;
-  while (tail > 0 && work < (double)slots * (rows + m.item)) {
+  while (tail > 0 && (ragged > 0.0 || work < (double)slots * (rows + m.item))) {
     const std::pair<int64_t, int> x = get(--tail);
     work += (double)x.first * (x.second + m.item);
     tail_rows = std::max(tail_rows, x.second);
@@ -217,6 +226,7 @@ inline BatchUnits pick_batch(const BatchModel &m, int64_t slots, int cus, bool p
       time = (longest + m.item) *
              ((double)(units / slots) + (left ? std::max(m.alone, share) : 0.0));
     }
+    time *= 1.0 + ragged * std::min(longest, 100) * 0.01;
     if (best_time < 0.0 || time < best_time * 0.999) {
       best_time = time;
       best.zpb = zpb;
@@ -224,5 +234,12 @@ inline BatchUnits pick_batch(const BatchModel &m, int64_t slots, int cus, bool p
   }
   return best;
 }
+
+// Whether a plane, or the planes of a batch, count as ragged: not on 64 bytes in
+// rows or segments, and more than the last cache holds.
+inline bool ragged_plane(uintptr_t power, int64_t ld, int U) {
+  return ((power | (uintptr_t)(ld * 4) | (uintptr_t)U * 4) & 63) != 0;
+}
+constexpr int64_t kCachedPlane = (int64_t)1 << 28;
 
 }  // namespace fdas

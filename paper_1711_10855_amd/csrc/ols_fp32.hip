@@ -617,9 +617,11 @@ static constexpr OlsVariant make_variant(const char *name) {
             : Gm::L <= 2048 ? UnitModel{5.2, 0.66, 0.47, 0.86, 1.031, {1.11, 0.50}}
             : Gm::L <= 4096 ? UnitModel{5.2, 0.66, 0.47, 0.86, 1.031, {0.0, 0.0}}
                             : UnitModel{3.0, 0.40, 0.35, 0.81, 1.0, {0.0, 0.0}};
-  v.batch_model = Gm::L <= 512    ? BatchModel{25.8, 0.40, 0.14}
-                  : Gm::L <= 1024 ? BatchModel{2.0, 0.82, 0.47}
-                                  : BatchModel{4.6, 0.37, 0.82};
+  v.batch_model = Gm::L <= 256    ? BatchModel{25.8, 0.40, 0.14, 0.0, 0.0}
+                  : Gm::L <= 512  ? BatchModel{25.8, 0.40, 0.14, 0.91, 0.91}
+                  : Gm::L <= 1024 ? BatchModel{2.0, 0.82, 0.47, 0.0, 0.65}
+                  : Gm::L <= 2048 ? BatchModel{4.6, 0.37, 0.82, 0.0, 1.11}
+                                  : BatchModel{4.6, 0.37, 0.82, 0.0, 0.0};
   v.lay.L = Gm::L;
   v.lay.T = Gm::T;
   v.lay.E = Gm::E;

@@ -1169,7 +1169,7 @@ static OlsVariant make_mixed(const char *name, int precision) {
   // The forward FFT costs several templates' worth of time here.
   v.zpb_target = 72;
   v.model = {8.6, 0.39, 0.21, 0.87, 1.044, {0.0, 0.0}};
-  v.batch_model = SPLIT ? BatchModel{5.0, 0.5, 0.65} : BatchModel{8.0, 0.5, 0.65};
+  v.batch_model = SPLIT ? BatchModel{5.0, 0.5, 0.65, 0.0, 0.0} : BatchModel{8.0, 0.5, 0.65, 0.0, 0.0};
   v.lay.L = 4096;
   v.lay.T = 256;
   v.lay.E = 16;

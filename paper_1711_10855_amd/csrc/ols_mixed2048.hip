@@ -611,7 +611,7 @@ static OlsVariant make(const char *name, int precision) {
   v.split = 0;
   v.zpb_target = 72;
   v.model = {6.0, 0.64, 0.0, 0.59, 1.0, {0.0, 0.0}};
-  v.batch_model = {8.0, 0.5, 0.65};
+  v.batch_model = {8.0, 0.5, 0.65, 0.0, 0.0};
   v.lay.L = L;
   v.lay.T = 128;
   v.lay.E = 16;

@@ -514,11 +514,9 @@ static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *p
   const int64_t nseg = (nbins + pl->U - 1) / pl->U;
   if (nseg > INT_MAX / 2) return set_error(FDAS_ERR_UNSUPPORTED, "nbins %lld too large", (long long)nbins);
   const int64_t nsb = (nseg + pl->var->G - 1) / pl->var->G;
-  // (a plane of 256 MB is what the last cache holds)
   const bool detect = cand.count != nullptr;
-  const bool lines =
-      ((reinterpret_cast<uintptr_t>(power) | (uintptr_t)(ld * 4) | (uintptr_t)pl->U * 4) & 63) == 0;
-  const bool ragged = !detect && !lines && ld * pl->nz * 4 > ((int64_t)1 << 28);
+  const bool ragged = !detect && ld * pl->nz * 4 > kCachedPlane &&
+                      ragged_plane(reinterpret_cast<uintptr_t>(power), ld, pl->U);
   const UnitSplit split = launch_split(pl, nsb, detect, ragged);
   pl->last_zpb = split.n1 ? split.zpb1 : split.zpb2;
   const int64_t nzg = (pl->nz + split.zpb2 - 1) / split.zpb2;
@@ -597,10 +595,19 @@ static int series_desc(fdas_plan_t pl, const fdas_series &x, int i, SeriesDesc *
 // Items of a batch whose series at place k has get(k) = (segment groups, rows).
 // FDAS_ZPB and the autotuner fix one size for all.
 template <class Get>
-static BatchUnits batch_units(fdas_plan_t pl, int n, Get &&get) {
+static BatchUnits batch_units(fdas_plan_t pl, const fdas_series *series, int n, Get &&get) {
   if (pl->zpb_forced || plan_cus(pl) <= 0) return {0, pl->zpb};
   const int64_t slots = (int64_t)pl->cus * std::max(1, pl->var->batch_blocks_per_cu(pl->pair));
-  return pick_batch(pl->var->batch_model, slots, pl->cus, pl->pair, n, get);
+  const BatchModel &m = pl->var->batch_model;
+  double ragged = pl->U % 16 ? m.ragged_segments : m.ragged_rows;
+  if (ragged > 0.0) {
+    int64_t bytes = 0;  // of the ragged planes
+    for (int i = 0; i < n; ++i)
+      if (ragged_plane(reinterpret_cast<uintptr_t>(series[i].power), series[i].ld, pl->U))
+        bytes += series[i].nbins * 4 * (int64_t)(2.0 * series[i].zmax / pl->p.dz + 1.5);
+    if (bytes <= kCachedPlane) ragged = 0.0;
+  }
+  return pick_batch(m, slots, pl->cus, pl->pair, ragged, n, get);
 }
 
 // Sets a series' templates per item: near-equal groups of at most zpb.
@@ -678,7 +685,7 @@ int plan_convolve_batch(fdas_plan_t pl, const fdas_series *series, int nseries, 
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
   std::vector<SeriesDesc> sorted(nseries);
   for (int k = 0; k < nseries; ++k) sorted[k] = desc[order[k]];
-  const BatchUnits units = batch_units(pl, nseries, [&](int k) {
+  const BatchUnits units = batch_units(pl, series, nseries, [&](int k) {
     return std::make_pair((int64_t)((sorted[k].nseg + G - 1) / G), sorted[k].nz);
   });
   int64_t total = 0;
@@ -798,7 +805,7 @@ int plan_convolve_batch_noalloc(fdas_plan_t pl, const fdas_series *series, int n
   // largest first, ties in input order (the order the graph path uses)
   std::sort(order, order + nseries,
             [&](int a, int b) { return cost[a] > cost[b] || (cost[a] == cost[b] && a < b); });
-  const BatchUnits units = batch_units(pl, nseries, [&](int k) {
+  const BatchUnits units = batch_units(pl, series, nseries, [&](int k) {
     return std::make_pair((int64_t)groups[order[k]], rows[order[k]]);
   });
   void *base = nullptr;

@@ -17,12 +17,13 @@ PROGRAM = r"""
 using namespace fdas;
 typedef std::pair<int64_t, int> Series;
 // the same rule, each size summed series by series
-static BatchUnits plain(const BatchModel &m, long slots, int cus, bool pair, const std::vector<Series> &s) {
+static BatchUnits plain(const BatchModel &m, long slots, int cus, bool pair, double ragged,
+                        const std::vector<Series> &s) {
   const int n = (int)s.size();
   int rows = 0, tail = n, tail_rows = 1;
   for (auto &x : s) rows = std::max(rows, x.second);
   double work = 0.0, head = 0.0;
-  while (tail > 0 && work < (double)slots * (rows + m.item)) {
+  while (tail > 0 && (ragged > 0.0 || work < (double)slots * (rows + m.item))) {
     --tail;
     work += (double)s[tail].first * (s[tail].second + m.item);
     tail_rows = std::max(tail_rows, s[tail].second);
@@ -48,6 +49,7 @@ static BatchUnits plain(const BatchModel &m, long slots, int cus, bool pair, con
       const double share = (double)((left + cus - 1) / cus * cus) / (double)slots;
       time = (longest + m.item) * ((double)(units / slots) + (left ? std::max(m.alone, share) : 0.0));
     }
+    time *= 1.0 + ragged * std::min(longest, 100) * 0.01;
     if (best_time < 0.0 || time < best_time * 0.999) best_time = time, best.zpb = zpb;
   }
   return best;
@@ -60,14 +62,15 @@ int main(int argc, char **argv) {
     const int n = 1 + next(most);
     std::vector<Series> s;
     for (int k = 0; k < n; ++k) s.push_back({1 + next(1 + next(300)), 1 + 7 * next(kinds)});
-    const BatchModel m{2.0 + next(25), 0.3 + 0.1 * next(8), 0.1 + 0.1 * next(8)};
+    const BatchModel m{2.0 + next(25), 0.3 + 0.1 * next(8), 0.1 + 0.1 * next(8), 0.0, 0.0};
     const long slots = 256l << next(5);
     const bool pair = next(2);
     long reads = 0;
-    const BatchUnits a = pick_batch(m, slots, 256, pair, n, [&](int k) { return ++reads, s[k]; });
+    const double ragged = next(3) ? 0.0 : 0.9;
+    const BatchUnits a = pick_batch(m, slots, 256, pair, ragged, n, [&](int k) { return ++reads, s[k]; });
     if (reads > 3l * n) return std::printf("%ld reads of %d series\n", reads, n), 1;
     if (a.tail < 0 || a.tail > n || a.zpb < 1) return std::printf("%d %d\n", a.tail, a.zpb), 1;
-    const BatchUnits b = plain(m, slots, 256, pair, s);
+    const BatchUnits b = plain(m, slots, 256, pair, ragged, s);
     if (kinds <= 64 && (a.tail != b.tail || a.zpb != b.zpb))
       return std::printf("trial %d: %d %d, not %d %d\n", trial, a.tail, a.zpb, b.tail, b.zpb), 1;
   }
