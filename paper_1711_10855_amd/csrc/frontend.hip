@@ -19,7 +19,8 @@
 //      median is 0) and A[0] = 0.
 // Every step is a kernel on the caller's stream; nothing returns to the host.
 //
-// Five launches (three for short series), each of which waits for the one
+// Five launches (three for short series; four for those of one transform: clear,
+// transform, real split, select and normalise), each of which waits for the one
 // before, so their number and the chain inside each are what a short series
 // costs, and passes over memory what a long one costs:
 //   columns   transforms over n1 of a few neighbouring columns, read and
@@ -31,7 +32,7 @@
 //   histogram (second digit), histogram (third digit): each block of these
 //             and of the last kernel finds the previous digit for itself from
 //             the finished histogram, which is cheaper than a kernel between;
-//   normalise (for short series the last three are one kernel).
+//   normalise (up to 2^16 bins the last three are one kernel).
 // As 13 launches with three transposes and a one-block kernel per digit: 142 us
 // for 2^22 samples and 60 us for 2^16, against 50 and 17. At 2^22 samples the
 // two transform kernels take 14 and 17 us for 33 and 41 MB each: what bounds
@@ -548,7 +549,8 @@ hipError_t launch_rows(const FrontendGeom &g, const c32 *work, c32 *spectrum, fl
 // -> 3.7 us and rows 8.2 -> 4.8 us at 32768 bins). That makes more stages, whose
 // factors come with their rounding errors (FINE), or the error would grow: over
 // 400 series of 2^16 samples 1.379e-7 of the spectrum's norm with 16 elements,
-// 1.421e-7 with few, and 1.376e-7 this way, in the same time.
+// 1.421e-7 with few, and 1.376e-7 this way (16.9 -> 17.0 us there, 24.4 -> 25.0 at
+// 2^19, where the gain of few elements is the least).
 constexpr int64_t kFewPoints = 1 << 18;
 template <class F>
 hipError_t with_length(int n, int64_t M, F &&f) {

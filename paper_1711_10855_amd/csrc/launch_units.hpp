@@ -238,7 +238,7 @@ inline BatchUnits pick_batch(const BatchModel &m, int64_t slots, int cus, bool p
 // Whether a plane, or the planes of a batch, count as ragged: not on 64 bytes in
 // rows or segments, and more than the last cache holds.
 inline bool ragged_plane(uintptr_t power, int64_t ld, int U) {
-  return ((power | (uintptr_t)(ld * 4) | (uintptr_t)U * 4) & 63) != 0;
+  return ((power | (uintptr_t)ld * 4 | (uintptr_t)U * 4) & 63) != 0;
 }
 constexpr int64_t kCachedPlane = (int64_t)1 << 28;
 

@@ -515,7 +515,7 @@ static int plan_launch(fdas_plan_t pl, const void *spec, int64_t nbins, float *p
   if (nseg > INT_MAX / 2) return set_error(FDAS_ERR_UNSUPPORTED, "nbins %lld too large", (long long)nbins);
   const int64_t nsb = (nseg + pl->var->G - 1) / pl->var->G;
   const bool detect = cand.count != nullptr;
-  const bool ragged = !detect && ld * pl->nz * 4 > kCachedPlane &&
+  const bool ragged = !detect && 4.0 * (double)ld * pl->nz > (double)kCachedPlane &&
                       ragged_plane(reinterpret_cast<uintptr_t>(power), ld, pl->U);
   const UnitSplit split = launch_split(pl, nsb, detect, ragged);
   pl->last_zpb = split.n1 ? split.zpb1 : split.zpb2;
