@@ -1,6 +1,6 @@
 """FP64 CPU oracle for the FDAS correlation step (test infrastructure only).
 
-This package is the checker, not the product. Only ``tests/``, the smoke
+This package is the oracle, not the product. Only ``tests/``, the smoke
 check in ``__graft_entry__`` and the ``cpu_baseline`` leg of ``bench.py``
 may import it. It shares no code with the HIP path: nothing here imports the
 package ``paper_1711_10855_amd`` and nothing there imports this package.

@@ -34,8 +34,8 @@
 //             the finished histogram, which is cheaper than a kernel between;
 //   normalise (up to 2^16 bins the last three are one kernel).
 // As 13 launches with three transposes and a one-block kernel per digit: 142 us
-// for 2^22 samples and 60 us for 2^16, against 50 and 17. At 2^22 samples the
-// two transform kernels take 14 and 17 us for 33 and 41 MB each: what bounds
+// for 2^22 samples and 60 us for 2^16, against 52 and 17. At 2^22 samples the
+// two transform kernels take 14 and 19 us for 33 and 41 MB each: what bounds
 // them is the 32-byte pieces in which the columns lie, one round of blocks with
 // nothing to cover its loads and stores.
 #include <hip/hip_runtime.h>

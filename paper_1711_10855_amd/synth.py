@@ -1,7 +1,7 @@
 """Seeded synthetic inputs for the FDAS correlation step.
 
 This module holds the workload recipes and the seeded input generators that
-both the checker and the HIP path consume. It contains none of the method's
+both the oracle and the HIP path consume. It contains none of the method's
 arithmetic (no templates, no correlation): it produces time series of white
 noise with injected accelerated sinusoids and turns them into the normalised
 complex spectrum the correlation step reads.
